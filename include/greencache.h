@@ -98,8 +98,7 @@ typedef enum gc_tiling {
                              (decode-like batches); otherwise wide or prefill tiles,
                              by the amount of work (see gc_prefix_prefill_plan) */
     GC_TILES_PREFILL = 1, /* 128 query rows x 64 keys per tile, staged through LDS */
-    GC_TILES_SMALL = 2,   /* 16 query rows x 32 keys per wavefront, read straight from
-                             global memory; needs Hq / Hkv <= 16 */
+    GC_TILES_SMALL = 2,   /* 16 query rows x 32 keys per wavefront; needs Hq / Hkv <= 16 */
     GC_TILES_WIDE = 3     /* 256 query rows x 64 keys per workgroup of 8 wavefronts,
                              staged through LDS (twice the rows per copied K/V tile) */
 } gc_tiling;

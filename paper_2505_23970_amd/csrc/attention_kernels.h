@@ -783,10 +783,6 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void attention_append_kernel
     attention_body<D, WAVES, false, true>(a, blockIdx.x);
 }
 
-// Merge the key chunks of one split query tile: with m = max_s lse_s,
-// lse = m + log sum_s exp(lse_s - m) and o = sum_s exp(lse_s - m) o_s / sum_s exp(lse_s - m),
-// in a fixed chunk order (deterministic).
-
 // Resident launch (wide tiles): one workgroup per compute unit, each
 // taking work items until none is left. Queue x holds the regular launch's indices
 // x, x + 8, x + 16, ...: the hardware deals workgroups to the eight XCDs in turn, so
@@ -830,17 +826,25 @@ __global__ __launch_bounds__(kWideWaves * 64, 1) void attention_resident_kernel(
     }
 }
 
-// A workgroup merges kCombineRows rows of one (query tile, KV head); a thread
-// owns four consecutive output elements of one row, so the partial rows are
-// read with coalesced 16-byte loads.
-template <int D>
+// Merge the key chunks of one split query tile: with m = max_s lse_s,
+// lse = m + log sum_s exp(lse_s - m) and o = sum_s exp(lse_s - m) o_s / sum_s exp(lse_s - m),
+// in a fixed order (deterministic). A thread owns four consecutive
+// output elements of one row, so the partial rows are read with coalesced 16-byte loads.
+// What bounds it is the round trips of dependent loads, not the bytes: chunks and their
+// log-sum-exps are read kBatch at a time in one pass with a running maximum, and with
+// S > 1 a row's chunks are dealt to S groups of threads (chunk s to group s % S) whose
+// results are joined through LDS in group order.
+template <int D, int S>
 __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const CombineArgs a) {
-    constexpr int CPR = D / 4;                      // float4 chunks per row
-    constexpr int kRows = kCombineThreads / CPR;    // rows per workgroup
+    constexpr int CPR = D / 4;                          // float4 chunks per row
+    constexpr int kRows = kCombineThreads / (CPR * S);  // rows per workgroup
+    __shared__ f32x4 s_acc[S > 1 ? kCombineThreads : 1];
+    __shared__ float s_max[S > 1 ? kCombineThreads / CPR : 1], s_tot[S > 1 ? kCombineThreads / CPR : 1];
     const int groups = ceil_div(a.block_m, kRows);
     const unsigned tile = blockIdx.x / (unsigned)groups;
-    const int m = (int)(blockIdx.x % (unsigned)groups) * kRows + (int)threadIdx.x / CPR;
-    if (m >= a.block_m) return;
+    const int lane_row = (int)threadIdx.x / CPR;        // (row, group) of this thread
+    const int sub = lane_row % S;
+    const int m = (int)(blockIdx.x % (unsigned)groups) * kRows + lane_row / S;
     const int c4 = (int)threadIdx.x % CPR;
     const int kvh = (int)(tile % (unsigned)a.num_kv_heads);
     const CombineItem ci = a.combines[tile / (unsigned)a.num_kv_heads];
@@ -851,39 +855,60 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const CombineA
     const int n = a.cu_new_lens[ci.r + 1] - cu;
     if (ci.q0 >= n) return;
     const int ntok = min(a.tq, n - ci.q0);
-    const int t = m / a.group, hl = m - t * a.group;
-    if (t >= ntok) return;
-    const int64_t row0 = ((int64_t)ci.part_base * a.num_kv_heads + kvh) * a.block_m + m;
-    const int64_t split_stride = (int64_t)a.num_kv_heads * a.block_m;  // rows between chunks
-    // chunks are read kBatch at a time with independent loads (the merge is bound by
-    // memory latency, not arithmetic); the sums still run in chunk order
-    constexpr int kBatch = 8;
-    float mx = -INFINITY;
-    for (int s0 = 0; s0 < ci.ns; s0 += kBatch) {
-        float l[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u)
-            l[u] = s0 + u < ci.ns ? a.part_lse[row0 + (s0 + u) * split_stride] : -INFINITY;
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) mx = fmaxf(mx, l[u]);
-    }
-    float tot = 0.f;
+    const int t = (int)((unsigned)m / (unsigned)a.group), hl = m - t * a.group;
+    const bool row_ok = m < a.block_m && t < ntok;
+    if (S == 1 && !row_ok) return;
+    float mx = -INFINITY, tot = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < ci.ns; s0 += kBatch) {
-        float l[kBatch];
-        f32x4 v[kBatch];
+    if (row_ok) {
+        const int64_t row0 = ((int64_t)ci.part_base * a.num_kv_heads + kvh) * a.block_m + m;
+        const int64_t split_stride = (int64_t)a.num_kv_heads * a.block_m;  // rows between chunks
+        constexpr int kBatch = S > 1 ? 4 : 8;
+        for (int s0 = sub; s0 < ci.ns; s0 += kBatch * S) {
+            float l[kBatch];
+            f32x4 v[kBatch];
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const bool ok = s0 + u < ci.ns;
-            const int64_t pr = row0 + (int64_t)(ok ? s0 + u : s0) * split_stride;
-            l[u] = ok ? a.part_lse[pr] : -INFINITY;
-            v[u] = *reinterpret_cast<const f32x4*>(a.part_o + pr * D + 4 * c4);
+            for (int u = 0; u < kBatch; ++u) {
+                const bool ok = s0 + u * S < ci.ns;
+                const int64_t pr = row0 + (int64_t)(ok ? s0 + u * S : s0) * split_stride;
+                l[u] = ok ? a.part_lse[pr] : -INFINITY;
+                v[u] = *reinterpret_cast<const f32x4*>(a.part_o + pr * D + 4 * c4);
+            }
+            float mn = mx;
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) mn = fmaxf(mn, l[u]);
+            const float off = mn == -INFINITY ? 0.f : mn;  // (chunks in which the row sees no key)
+            const float alpha = expf(mx - off);
+            tot *= alpha;
+            acc *= alpha;
+            mx = mn;
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const float w = expf(l[u] - off);  // 0 for the padding entries
+                tot += w;
+                acc += w * v[u];
+            }
         }
+    }
+    if constexpr (S > 1) {
+        s_acc[threadIdx.x] = acc;
+        if (c4 == 0) {
+            s_max[lane_row] = mx;
+            s_tot[lane_row] = tot;
+        }
+        __syncthreads();
+        if (sub != 0 || !row_ok) return;
+        const float mx0 = mx;
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) {
-            const float w = expf(l[u] - mx);  // 0 for the padding entries
-            tot += w;
-            acc += w * v[u];
+        for (int g = 1; g < S; ++g) mx = fmaxf(mx, s_max[lane_row + g]);
+        const float w0 = expf(mx0 - mx);
+        tot *= w0;
+        acc *= w0;
+#pragma unroll
+        for (int g = 1; g < S; ++g) {
+            const float w = expf(s_max[lane_row + g] - mx);
+            tot += w * s_tot[lane_row + g];
+            acc += w * s_acc[threadIdx.x + g * CPR];
         }
     }
     const float lse_tot = mx + logf(tot);

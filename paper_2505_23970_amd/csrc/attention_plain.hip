@@ -48,13 +48,27 @@ hipError_t launch_attention_append(const AttnArgs& a, int head_dim, int64_t num_
     return hipGetLastError();
 }
 
-hipError_t launch_combine(const CombineArgs& a, int head_dim, int64_t num_combines, hipStream_t s) {
-    const int groups = ceil_div(a.block_m, kCombineThreads / (head_dim / 4));
-    const dim3 grid((unsigned)(num_combines * a.num_kv_heads * groups));
-    if (head_dim == 128)
-        combine_kernel<128><<<grid, kCombineThreads, 0, s>>>(a);
-    else
-        combine_kernel<64><<<grid, kCombineThreads, 0, s>>>(a);
+hipError_t launch_combine(const CombineArgs& a, int head_dim, int64_t num_combines, int max_splits, hipStream_t s) {
+    // Eight thread groups per row save round trips (32 chunks each instead of 8, about
+    // 1 us a trip) and cost workgroups (one per row instead of one per eight, about 0.7 ns
+    // each to start), so they are for few rows: 16.3 -> 15.1 us (attention and merge) for
+    // 128 rows of 17 chunks, but 28.6 -> 31.0 for 4096 rows of 9 and 93 -> 105 for 16384.
+    const int64_t all_rows = num_combines * a.num_kv_heads * a.block_m;
+    const int trips_saved = ceil_div(max_splits, 8) - ceil_div(max_splits, 32);
+    const int groups_of = all_rows <= 1536LL * trips_saved ? 8 : 1;
+    const int rows = kCombineThreads / (head_dim / 4 * groups_of);
+    const dim3 grid((unsigned)(num_combines * a.num_kv_heads * ceil_div(a.block_m, rows)));
+    if (head_dim == 128) {
+        if (groups_of > 1)
+            combine_kernel<128, 8><<<grid, kCombineThreads, 0, s>>>(a);
+        else
+            combine_kernel<128, 1><<<grid, kCombineThreads, 0, s>>>(a);
+    } else {
+        if (groups_of > 1)
+            combine_kernel<64, 8><<<grid, kCombineThreads, 0, s>>>(a);
+        else
+            combine_kernel<64, 1><<<grid, kCombineThreads, 0, s>>>(a);
+    }
     return hipGetLastError();
 }
 

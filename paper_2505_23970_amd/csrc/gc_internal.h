@@ -14,10 +14,9 @@ constexpr int kWaves = 4;
 constexpr int kBlockM = kRowsPerWave * kWaves;  // 128
 constexpr int kBlockN = 64;
 // Small-tile (decode) path: one wavefront owns 16 query rows and walks the keys
-// in tiles of 32 (two pages), straight from global memory.
+// in tiles of 32 (two pages) through an LDS ring of its own.
 constexpr int kDecM = 16;
 constexpr int kDecN = 32;
-constexpr int kDecWaves = 4;                    // independent wavefronts per workgroup
 constexpr int kPage = 16;
 constexpr int kAttnThreads = kWaves * 64;
 // Wide prefill tiles: 8 wavefronts, 256 query rows per work item (one workgroup
@@ -230,6 +229,7 @@ hipError_t launch_attention_small(const AttnArgs& a, int head_dim, int64_t num_i
                                   hipStream_t s);
 hipError_t launch_read_probe(const void* buf, size_t bytes, uint32_t* sink, hipStream_t s);
 hipError_t launch_mfma_probe(int iterations, float* sink, hipStream_t s);
-hipError_t launch_combine(const CombineArgs& a, int head_dim, int64_t num_combines, hipStream_t s);
+// max_splits: the most key chunks of any split query tile
+hipError_t launch_combine(const CombineArgs& a, int head_dim, int64_t num_combines, int max_splits, hipStream_t s);
 
 }  // namespace gc
