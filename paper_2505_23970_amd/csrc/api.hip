@@ -152,14 +152,17 @@ int device_cus() {
 // Split policy: keep whole query tiles when there are at least as many work
 // items as resident slots (per compute unit: two 128-row workgroups, one wide
 // workgroup, or four small-tile wavefronts); otherwise cut the keys into chunks
-// so that the launch fills those slots.
-//   Prefill and wide tiles: equal shares of the key tiles, at least 512 keys.
-//   Small tiles: the smallest chunk that still makes no more items than slots, so
-// that no few leftover items run a round of their own, and at least 384 keys.
+// so that the launch fills those slots: the smallest chunk that makes no more items
+// than slots (each query tile's chunks are rounded up, so equal shares of the key
+// tiles make a few items more, which run a round of their own), and at least 512 keys
+// (384 for small tiles), below which the partial rows and a work item's fixed cost
+// outweigh the shorter chunks.
 // Measured on MI355X (attention and merge, 70B heads): one request of 4100 tokens
 // 15.9 us with chunks of 384 keys (24.3 with 1024), four requests of 61 MB of codes
 // 18.1 us (29.4 with 1024, 21.5 with 128); 32 requests of 791 MB 145 us with 1000
-// items (155 with 1150, 162 with 4000).
+// items (155 with 1150, 162 with 4000). 16 requests of 4 to 64 new tokens on 4000
+// cached ones: 85 us with 480 128-row items (103 with the 600 of equal shares, 97 with
+// 1000); one request of 512 on 8000: 137 us with 256 wide items (165 with 288).
 constexpr int kSmallMinChunkKeys = 384;
 int64_t resident_slots(const Shape& sh) { return (sh.small ? 4LL : (sh.wide ? 1LL : 2LL)) * device_cus(); }
 
@@ -184,24 +187,20 @@ int choose_chunk(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
     int64_t chunk = (tiles + target - 1) / target;
     const int min_keys = sh.small ? kSmallMinChunkKeys : 512;
     if (chunk < min_keys / sh.block_n) chunk = min_keys / sh.block_n;
-    if (sh.small) {
-        // (each query tile's chunks are rounded up, so equal shares make more items)
-        auto items = [&](int64_t ch) {
-            int64_t k = 0;
-            for (int r = 0; r < b->batch; ++r) {
-                const int P = b->prefix_lens_host[r], n = b->new_lens_host[r];
-                for (int q0 = 0; q0 < n; q0 += sh.tq)
-                    k += gc::ceil_div64(gc::key_tiles(P, q0, n - q0 < sh.tq ? n - q0 : sh.tq, sh.block_n), ch);
-            }
-            return k * geo->num_kv_heads;
-        };
-        int64_t lo = chunk, hi = max_tiles;  // unsplit tiles: units < target items
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) / 2;
-            if (items(mid) <= target) hi = mid;
-            else lo = mid + 1;
+    auto items = [&](int64_t ch) {
+        int64_t k = 0;
+        for (int r = 0; r < b->batch; ++r) {
+            const int P = b->prefix_lens_host[r], n = b->new_lens_host[r];
+            for (int q0 = 0; q0 < n; q0 += sh.tq)
+                k += gc::ceil_div64(gc::key_tiles(P, q0, n - q0 < sh.tq ? n - q0 : sh.tq, sh.block_n), ch);
         }
-        chunk = lo;
+        return k * geo->num_kv_heads;
+    };
+    int64_t hi = max_tiles;  // unsplit tiles: units < target items
+    while (chunk < hi) {
+        const int64_t mid = (chunk + hi) / 2;
+        if (items(mid) <= target) hi = mid;
+        else chunk = mid + 1;
     }
     return chunk > INT32_MAX ? 0 : (int)chunk;
 }

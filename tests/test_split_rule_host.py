@@ -1,0 +1,56 @@
+"""The automatic key split on the CPU (256 compute units assumed without a GPU): the
+workspace of the automatic plan is that of the smallest chunk, from the floor up, that
+makes no more work items than resident slots, for every tiling and ragged batches."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2505_23970_amd as gc
+from test_abi_host import HostBatch, geo
+
+# tiling: (query rows, keys per tile, slots per compute unit, least keys per chunk)
+RULES = {gc.TILES_SMALL: (16, 32, 4, 384), gc.TILES_PREFILL: (128, 64, 2, 512), gc.TILES_WIDE: (256, 64, 1, 512)}
+CUS = 256
+
+BATCHES = {
+    "one_long": ([32768], [1]),
+    "one_short": ([40], [3]),
+    "ragged_decode": ([20963, 530, 5723, 2601, 2852, 3447, 814, 3402] * 4, [1] * 32),
+    "documents": ([2679, 2063, 3533, 4936, 7059, 4226, 3034, 2702] * 2, [19, 11, 15, 16, 14, 26, 64, 4] * 2),
+    "empty_among": ([5000, 900, 0, 7000], [2, 0, 0, 30]),
+    "many": (list(range(100, 100 + 37 * 300, 37)), [1] * 300),
+}
+
+
+def tiles_of(P, n, tq, bn):
+    return [-(-(p + min(q0 + tq, m)) // bn) for p, m in zip(P, n) for q0 in range(0, m, tq)]
+
+
+def workspace(lib, g, desc, split, tiling):
+    size = ctypes.c_size_t()
+    opt = gc.PlanOptions(split, tiling)
+    assert lib.gc_prefix_prefill_workspace_size(ctypes.byref(g), ctypes.byref(desc), ctypes.byref(opt),
+                                                ctypes.byref(size)) == 0
+    return size.value
+
+
+@pytest.mark.parametrize("name", sorted(BATCHES))
+@pytest.mark.parametrize("tiling", sorted(RULES))
+@pytest.mark.parametrize("Hq,Hkv", [(64, 8), (8, 1), (12, 4)])
+def test_automatic_chunk_is_the_smallest_that_fits_the_slots(name, tiling, Hq, Hkv):
+    lib = gc.load_library()
+    P, n = BATCHES[name]
+    m, bn, per_cu, floor_keys = RULES[tiling]
+    kts = tiles_of(P, n, m // (Hq // Hkv), bn)
+    slots = per_cu * CUS
+    if len(kts) * Hkv >= slots:
+        chunk = -1                                   # enough whole query tiles
+    else:
+        chunk = max(floor_keys // bn, -(-sum(kts) * Hkv // slots))
+        while chunk < max(kts) and sum(-(-k // chunk) for k in kts) * Hkv > slots:
+            chunk += 1
+        assert sum(-(-k // chunk) for k in kts) * Hkv <= slots
+    b = HostBatch(np.array(P), np.array(n))
+    g = geo(Hq=Hq, Hkv=Hkv, maxb=2100)
+    assert workspace(lib, g, b.desc, 0, tiling) == workspace(lib, g, b.desc, chunk, tiling)
