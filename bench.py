@@ -168,7 +168,7 @@ V_SCALE_FP8 = 0.0213
 def auto_kernel_name(w, cus, fp8):
     """Kernel the library's automatic tiling picks for w, named as in the kernel trace
     (the rule of choose_tiling and resident_workgroups in the C ABI, restated: small
-    tiles when every request has n * g <= 16, else wide tiles when 256-row tiles are
+    tiles when every request has n * g <= 16, else at d = 128 wide tiles when 256-row tiles are
     >= 85 % full and their grid is not between one and two per compute unit, run as a
     resident launch from two rounds of work items on, else 128-row tiles)."""
     g = w.num_q_heads // w.num_kv_heads
@@ -181,7 +181,7 @@ def auto_kernel_name(w, cus, fp8):
     units = int(sum((int(n) + tq - 1) // tq for n in w.new_lens))
     rows = int(w.new_lens.sum()) * g
     grid = units * w.num_kv_heads
-    wide = rows * 100 >= units * 256 * 85 and not (cus < grid < 2 * cus)
+    wide = D == 128 and rows * 100 >= units * 256 * 85 and not (cus < grid < 2 * cus)
     if wide and cus % 8 == 0 and wide_items(w, cus) * w.num_kv_heads >= 2 * cus:
         # resident launch: one workgroup per CU taking the items from per-XCD queues
         return f"attention_resident_kernel<{D}, {f}>" + split

@@ -92,10 +92,13 @@ gc_status check_options(const gc_plan_options* o) {
 // wavefronts, one workgroup per CU) when they would be at least 85 % full and
 // their count is not between one and two per CU (whole units there would leave
 // the last round of workgroups mostly idle, and below one per CU the keys are
-// split into equal chunks); 128-row tiles otherwise.
+// split into equal chunks); 128-row tiles otherwise. Wide tiles save copies, which is
+// not what bounds d = 64 (half the products for the same weights: the vector unit);
+// three 128-row workgroups share a compute unit there (164 registers) and overlap better:
+// 16 misses of 100 to 1500 tokens 120 us against 148 on wide tiles.
 int device_cus();
 
-gc_status choose_tiling(const gc_batch* b, const gc_plan_options* o, int num_kv_heads, Shape* sh) {
+gc_status choose_tiling(const gc_geometry* geo, const gc_batch* b, const gc_plan_options* o, Shape* sh) {
     const int want = o == nullptr ? GC_TILES_AUTO : o->tiling;
     bool small = false, wide = false;
     if (want == GC_TILES_SMALL) {
@@ -109,7 +112,7 @@ gc_status choose_tiling(const gc_batch* b, const gc_plan_options* o, int num_kv_
             for (int r = 0; r < b->batch && small; ++r)
                 small = (int64_t)b->new_lens_host[r] * sh->group <= gc::kDecM;
         }
-        if (!small) {
+        if (!small && geo->head_dim == 128) {
             const int tq = gc::tokens_per_tile(sh->group, gc::kWideM);
             int64_t units = 0, rows = 0;
             for (int r = 0; r < b->batch; ++r) {
@@ -117,7 +120,7 @@ gc_status choose_tiling(const gc_batch* b, const gc_plan_options* o, int num_kv_
                 rows += (int64_t)b->new_lens_host[r] * sh->group;
             }
             const int64_t cus = device_cus();
-            const int64_t grid = units * num_kv_heads;
+            const int64_t grid = units * geo->num_kv_heads;
             wide = rows * 100 >= units * gc::kWideM * 85 && !(grid > cus && grid < 2 * cus);
         }
     }
@@ -269,7 +272,7 @@ gc_status plan_checked(const gc_geometry* geo, const gc_batch* b, const gc_plan_
     if (st != GC_OK) return st;
     st = check_options(o);
     if (st != GC_OK) return st;
-    st = choose_tiling(b, o, geo->num_kv_heads, sh);
+    st = choose_tiling(geo, b, o, sh);
     if (st != GC_OK) return st;
     if (sh->total_tokens == 0) return GC_OK;
     return make_plan(geo, b, *sh, o, pl);

@@ -9,15 +9,20 @@
 // Work decomposition. A workgroup (4 wavefronts, or 8 for the wide tiling) owns
 // one work item: 128 (256) query rows = the g query heads of one KV head stacked
 // over consecutive new tokens of one request, against a range of 64-key tiles.
-// Each wavefront owns 32 of the rows. Per key tile:
-//   S^T (64 keys x 32 rows)  = K_tile . Q^T        two 32x32 blocks, MFMA 32x32x16 bf16
+// Each wavefront owns 32 of the rows, as two blocks of 16. Per key tile:
+//   S^T (64 keys x 32 rows)  = K_tile . Q^T        4 x 2 blocks of 16x16, MFMA 16x16x32 bf16
 //   online softmax on S^T in registers               fp32, base-2 exponent
-//   O^T (D x 32 rows)       += V_tile^T . P^T       D/32 blocks, MFMA 32x32x16 bf16
-// Computing the transposed products puts every score of one query row in one
-// lane pair (lanes l and l+32), so row maxima and sums are in-lane plus one
-// cross-half exchange, and the QK^T accumulator doubles as the PV operand
-// once the key rows fed to the first product are permuted (bits 2 and 3 of
-// the row index swapped).
+//   O^T (D x 32 rows)       += V_tile^T . P^T       D/16 x 2 blocks, MFMA 16x16x32 bf16
+// Every K and V fragment read from LDS serves both row blocks. Computing the transposed
+// products puts the scores of one query row in four lanes (l, l + 16, l + 32, l + 48), so
+// row maxima and sums are in-lane plus two exchanges, and the QK^T accumulators double as
+// the PV operand once the key rows fed to the first product are permuted.
+// The 16x16x32 products are taken because these tiles run against the card's power limit
+// on real data (zero inputs: 370 us instead of 503 for the 32k reuse batch, at the same
+// instructions): a register loop of products on normal data sustains 2070 TFLOP/s with
+// 16x16x32 and 1800 with 32x32x16 (2460 with either on zeros). Kernel against kernel, 32k
+// reuse 483 -> 458 us, mixed 70B batch 2206 -> 2107, one request of 512 tokens on 8000
+// 137 -> 127.
 // K and V tiles are staged through LDS, double buffered: the next tile's
 // global loads are in flight while the current tile is computed. Value pages
 // are stored transposed in the pool ([D][16]), so both LDS tiles are read with
@@ -38,7 +43,6 @@ namespace gc {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -48,11 +52,14 @@ constexpr float kLn2 = 0.69314718055994530942f;
 // Buffer resource word 3 for raw (untyped) loads: 32-bit data format.
 constexpr int kBufferFlags = 0x00020000;
 
-// 16-byte chunk position inside an LDS row (conflict-free 16-lane reads).
+// Position of 16-byte chunk `chunk` inside key row `row` of a tile in LDS. A fragment
+// read takes, per 16 lanes, the rows 16 p + 8 h + 4 b + v (p, h = 0, 1, v = 0 .. 3) of one
+// block b at one chunk: the swizzle sends them to different banks.
 template <int D>
 __device__ __forceinline__ int swz_k(int chunk, int row) {
-    if constexpr (D == 128) return chunk ^ (row & 15);  // 256-byte rows
-    else return chunk ^ ((row >> 1) & 7);                // 128-byte rows
+    const int p = (row >> 4) & 1, h = (row >> 3) & 1;
+    if constexpr (D == 128) return chunk ^ (row & 15) ^ (4 * p);             // 256-byte rows
+    else return chunk ^ (((row >> 1) & 1) | (2 * p) | (4 * h));               // 128-byte rows
 }
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -133,8 +140,10 @@ template <int D, int WAVES, bool FP8, bool FUSE>
 __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned bid) {
     static_assert(!(FP8 && FUSE), "the fused append runs over bf16 pools");
     constexpr int kBlockRows = WAVES * kRowsPerWave;  // query rows of a work item
-    constexpr int DK = D / 16;                      // k-steps of QK^T
-    constexpr int DB = D / 32;                      // 32-row blocks of O^T
+    constexpr int KS = D / 32;                      // k-steps of QK^T
+    constexpr int DB = D / 16;                      // 16-row blocks of O^T
+    constexpr int RB = kRowsPerWave / 16;           // 16-row query blocks per wavefront
+    static_assert(RB == 2, "row blocks");
     constexpr int kPageBytes = kPage * D * 2;       // one (block, KV head) page of K or V
     constexpr int kTileBytes = kBlockN * D * 2;     // four pages
     constexpr int kKbPerPage = kPageBytes / 1024;   // 1 KiB pieces per page
@@ -158,8 +167,8 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     const int tid = tid_opaque;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int hh = lane >> 5;
-    const int lr = lane & 31;
+    const int g4 = lane >> 4;
+    const int j16 = lane & 15;
     const int kvh = (int)(bid % (unsigned)a.num_kv_heads);
     const WorkItem it = a.items[bid / (unsigned)a.num_kv_heads];
     // all eight fields in one load (else the fields the test below needs are loaded
@@ -167,6 +176,14 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     asm volatile("" ::"s"(it.r), "s"(it.q0), "s"(it.kt_begin), "s"(it.kt_end), "s"(it.part), "s"(it.P),
                  "s"(it.cu), "s"(it.n));
     if (it.r < 0 || it.kt_begin >= it.kt_end) return;
+    // One of a SIMD's two wavefronts is preferred throughout (the older half of a wide
+    // workgroup; over d = 128 every other 256 of the 128-row workgroups, two of which share a
+    // compute unit): the preferred one's products run while the other computes weights and
+    // the other way round, where equal ones take turns product by product and then wait
+    // for the vector unit together. Mixed 70B batch 2107 -> 2052 us, 70B chat 434 -> 422,
+    // 8B chat 125.7 -> 121.5, over 8-bit pools 173.6 -> 154.8; at d = 64, where three
+    // 128-row workgroups share a compute unit, 2 % slower, so not there.
+    if (WAVES == kWideWaves ? wave < WAVES / 2 : D == 128 && ((bid >> 8) & 1)) __builtin_amdgcn_s_setprio(2);
 
     // (the planner repeats the request's lengths in the item: one load for all of them)
     const int r = it.r;
@@ -176,13 +193,19 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     const int L = P + n;
     const int ntok = min(a.tq, n - it.q0);
 
-    // this lane's query row: token t of the tile, query head kvh * g + hl
-    const int m = wave * kRowsPerWave + lr;
-    const int t = m / a.group;
-    const int hl = m - t * a.group;
-    const bool row_ok = t < ntok;
-    const int lim = P + it.q0 + (row_ok ? t : 0);  // last key this row may see
-    const int64_t qrow = (int64_t)(cu + it.q0 + t) * a.num_q_heads + kvh * a.group + hl;
+    // this lane's query rows, 16 rb + j16 of the wavefront's 32: token t of the tile, query
+    // head kvh * g + hl
+    bool row_ok[RB];
+    int lim[RB];  // last key the row may see
+    int64_t qrow[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        const int m = wave * kRowsPerWave + 16 * rb + j16;
+        const int t = (int)((unsigned)m / (unsigned)a.group);
+        row_ok[rb] = t < ntok;
+        lim[rb] = P + it.q0 + (row_ok[rb] ? t : 0);
+        qrow[rb] = (int64_t)(cu + it.q0 + t) * a.num_q_heads + kvh * a.group + (m - t * a.group);
+    }
 
     // block-table entries of the first key tile, loaded before Q: loads return in
     // order, so the first tile's copies then wait for these entries only and go out
@@ -190,15 +213,18 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     // the row, checked at use)
     int ids = a.block_tables[(int64_t)r * a.max_blocks + min(it.kt_begin * 4 + (lane & 3), a.max_blocks - 1)];
 
-    // Q^T operand: lane holds q[row][16k + 8*hh .. +7]
-    bf16x8 qf[DK];
-    if (row_ok) {
-        const uint16_t* qp = a.q + qrow * D + hh * 8;
+    // Q^T operands: lane holds q[row 16 rb + j16][32 ks + 8 g4 .. +7]
+    bf16x8 qf[RB][KS];
 #pragma unroll
-        for (int k = 0; k < DK; ++k) qf[k] = *reinterpret_cast<const bf16x8*>(qp + 16 * k);
-    } else {
+    for (int rb = 0; rb < RB; ++rb) {
+        if (row_ok[rb]) {
+            const uint16_t* qp = a.q + qrow[rb] * D + g4 * 8;
 #pragma unroll
-        for (int k = 0; k < DK; ++k) qf[k] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+            for (int k = 0; k < KS; ++k) qf[rb][k] = *reinterpret_cast<const bf16x8*>(qp + 32 * k);
+        } else {
+#pragma unroll
+            for (int k = 0; k < KS; ++k) qf[rb][k] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+        }
     }
 
     // Direct global->LDS loads: instruction e of a wave moves 1 KiB piece 4e + wave of
@@ -207,8 +233,13 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     static_assert(WAVES % kKbPerPage == 0, "piece layout");
     auto page_of = [&](int e) -> int { return (WAVES / kKbPerPage) * e + (wave & (WAVES - 1)) / kKbPerPage; };
     const int k_row = sub * (1024 / (2 * D)) + lane / (D / 8);         // key slot in the page
-    const uint32_t k_chunk = swz_k<D>(lane % (D / 8), k_row) * 16;     // source chunk of the row
-    const uint32_t k_src = k_row * (2 * D) + k_chunk;
+    // source chunk of the row, by the parity of the page in the tile (that of e where the
+    // pieces of one instruction cover one page, else the wavefront's own)
+    auto parity = [&](int e) { return (WAVES / kKbPerPage) % 2 == 1 ? e & 1 : (wave / kKbPerPage) & 1; };
+    auto k_chunk = [&](int e) -> uint32_t { return swz_k<D>(lane % (D / 8), 16 * parity(e) + k_row) * 16; };
+    uint32_t k_src[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) k_src[e] = k_row * (2 * D) + k_chunk(e);
     const int v_d = sub * 32 + (lane >> 1);                            // value row (d) in the page
     const int v_half = (lane & 1) ^ ((v_d >> 3) & 1);                  // logical half held by the lane
     const uint32_t v_src = v_d * 32 + v_half * 16;
@@ -252,7 +283,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     };
     auto issue_plain = [&](int buf, const int64_t off, int e) {
         const uint32_t at = page_of(e) * kPageBytes + lds_piece;
-        dma16(kpool + off, k_src, lds_address(buf ? k_lds1 : k_lds0) + at);
+        dma16(kpool + off, k_src[e & 1], lds_address(buf ? k_lds1 : k_lds0) + at);
         dma16(vpool + off, v_src, lds_address(buf ? v_lds1 : v_lds0) + at);
     };
     auto issue_page = [&](int buf, int kt, const int blk, int e) {
@@ -265,10 +296,10 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
             issue_plain(buf, page_offset(kt, blk, e), e);
         } else if (ok) {
             const int64_t base = (int64_t)blk * block_stride + head_off;
-            const unsigned char* ks = kpool + base + k_src;
+            const unsigned char* ks = kpool + base + k_src[e & 1];
             if (lp * kPage + kPage > P) {           // the page holds new keys
                 const int pos = lp * kPage + k_row;  // this lane's key
-                if (pos >= P && pos < L) ks = k_new_h + (int64_t)(pos - P) * new_stride + k_chunk;
+                if (pos >= P && pos < L) ks = k_new_h + (int64_t)(pos - P) * new_stride + k_chunk(e);
             }
             dma16(ks, kdst + pg * kPageBytes + sub * 1024);
             if (lp * kPage < P) dma16(vpool + base + v_src, vdst + pg * kPageBytes + sub * 1024);
@@ -364,12 +395,11 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         }
     };
 
-    f32x16 o[DB];
-    float m_run;   // exponent offset (score * scale * log2(e) units)
-    float neg_off; // -m_run, 0 while the row has none
-    bool need_max; // some row has no offset yet, or the exact pass
-    float l_run;   // this lane's half of the row sum of the bf16 weights,
-    float l_run1;  // accumulated in two independent sums
+    f32x4 o[RB][DB];
+    float m_run[RB];   // exponent offset (score * scale * log2(e) units)
+    float neg_off[RB]; // -m_run, 0 while the row has none
+    bool need_max;     // some row has no offset yet, or the exact pass
+    float l_run[RB];   // this lane's share of the row sum of the bf16 weights
     // Exponent offset: a row takes the maximum of its first tile with a visible key and
     // keeps it; the weights of later tiles are exp2 of up to ~100 and fp32 holds their
     // products and sums. If some row's sum leaves that range (a score jump of more than
@@ -378,131 +408,157 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     // normalisation uses the same offset, so the result does not depend on it.
     bool exact = false;
     const float c = a.scale_log2;
-    // key row fed to the QK^T product by this lane: bits 2 and 3 of lr swapped
-    const int prow = (lr & 0x13) | ((lr & 4) << 1) | ((lr & 8) >> 1);
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 
-    // LDS fragment reads kept in flight ahead of their MFMA (fewer when 8-bit codes
-    // for the next tile occupy registers during the products; five for bf16 pools at
-    // d = 128, measured 0.6-2 % faster than six on the long-prefix workloads)
-    constexpr int kAhead = (!FP8 && !FUSE && D == 128) ? 5 : ((FP8 || FUSE) && WAVES == 4 && D == 128) ? 4 : 6;
-    // (value fragments: four on the 8-wavefront bf16 tiles at d = 128, where the weights
-    // computed between the PV products keep the wavefront busy meanwhile)
-    constexpr int kAheadV = (!FP8 && !FUSE && D == 128 && WAVES == 8) ? 4 : kAhead;
-    // hook(i) runs after the i-th QK^T product is issued (the next tile's copies go there)
+    // Lane group G of the score accumulators holds keys 16 (G % 2) + 8 (G / 2) .. + 7 of
+    // each 32-key half of a tile: accumulator v of block b is the (4 b + v)-th of them. The
+    // K rows are fed to the products in that order, so that the accumulators are already
+    // the P^T operand and the V^T operand is eight adjacent slots of one page.
+    const int key_lane = kPage * (g4 & 1) + 8 * (g4 >> 1);
+    // K^T operand of (half hb, block b, k-step ks): lane j16 = 4 G + v reads chunk
+    // 4 ks + g4 of its row; block 1's rows are 4 further (for d = 128 with the chunk
+    // swizzled by 4 more), a half's 32 further.
+    constexpr int kRow = 2 * D;
+    uint32_t k_at[KS];
+    {
+        const int r0 = kPage * ((j16 >> 2) & 1) + 8 * (j16 >> 3) + (j16 & 3);
+#pragma unroll
+        for (int x = 0; x < KS; ++x) k_at[x] = (uint32_t)(r0 * kRow + swz_k<D>(g4, r0) * 16) ^ (64u * x);
+    }
+    // V^T operand of (half hb, block db): value row 16 db + j16, this lane's eight slots
+    const uint32_t v_at = (uint32_t)((g4 & 1) * kPageBytes + j16 * 32 + 16 * ((g4 >> 1) ^ (j16 >> 3)));
+
+    // LDS fragment reads kept in flight ahead of their products (three and five within 1 %,
+    // eight 1-10 % slower)
+    constexpr int kAhead = 4;
+    // hook(i) runs after the products of the i-th K fragment are issued (the next tile's copies go there)
     auto compute_tile = [&](const unsigned char* kb, const unsigned char* vb, int kt, auto&& hook) {
-        // S^T = K_tile . Q^T: MFMA i uses K fragment (k = i/2, block b = i%2). Every
-        // group below is fenced so the fragment reads stay kAhead MFMAs ahead.
-        bf16x8 kf[2 * DK];
+        // S^T = K_tile . Q^T: fragment i is (half i / 2 KS, k-step, block i % 2), used for
+        // both row blocks. Every group below is fenced so the fragment reads stay kAhead
+        // fragments ahead.
+        constexpr int NK = 4 * KS;
+        bf16x8 kf[NK];
         auto kread = [&](int i) {
-            const int k = i >> 1, b = i & 1;
-            const int krow = 32 * b + prow;
-            kf[i] = *reinterpret_cast<const bf16x8*>(kb + krow * (2 * D) + swz_k<D>(2 * k + hh, krow) * 16);
+            const int hb = i / (2 * KS), ks = (i >> 1) % KS, b = i & 1;
+            const int x = D == 128 ? ks ^ b : ks;
+            kf[i] = *reinterpret_cast<const bf16x8*>(kb + (32 * hb + 4 * b) * kRow + k_at[x]);
         };
-        f32x16 s[2] = {f32x16{}, f32x16{}};
+        f32x4 s[RB][2][2];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) s[rb][hb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) kread(i);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < 2 * DK; ++i) {
-            if (i + kAhead < 2 * DK) kread(i + kAhead);
-            s[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[i >> 1], s[i & 1], 0, 0, 0);
+        for (int i = 0; i < NK; ++i) {
+            const int hb = i / (2 * KS), ks = (i >> 1) % KS, b = i & 1;
+            if (i + kAhead < NK) kread(i + kAhead);
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+                s[rb][hb][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[i], qf[rb][ks], s[rb][hb][b], 0, 0, 0);
             hook(i);
             __builtin_amdgcn_sched_barrier(0);
         }
-        // V fragments of the first value page go out now; they land during the softmax
-        bf16x8 vf[4 * DB];
+        // the first V fragments go out now; they land during the softmax
+        bf16x8 vf[2 * DB];
         auto vread = [&](int i) {
-            const int st = i / DB, db = i % DB;
-            const int d = 32 * db + lr;
-            vf[i] = *reinterpret_cast<const bf16x8*>(vb + st * kPageBytes + d * 32 + ((hh ^ ((d >> 3) & 1)) * 16));
+            vf[i] = *reinterpret_cast<const bf16x8*>(vb + (i / DB) * 2 * kPageBytes + (i % DB) * 512 + v_at);
         };
 #pragma unroll
-        for (int i = 0; i < kAheadV; ++i) vread(i);
+        for (int i = 0; i < kAhead; ++i) vread(i);
         __builtin_amdgcn_sched_barrier(0);
 
-        // s[b][e] is the score of tile key 32b + 16(e>>3) + 8hh + (e&7)
+        // s[rb][hb][b][v] is the score of row 16 rb + j16 and tile key 32 hb + key_lane + 4 b + v
         const int key0 = kt * kBlockN;
         if (key0 + kBlockN - 1 > P + it.q0) {
-            const int rel = lim - key0 - 8 * hh;
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
+            for (int rb = 0; rb < RB; ++rb) {
+                const int rel = lim[rb] - key0 - key_lane;
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    s[b][e] = (32 * b + 16 * (e >> 3) + (e & 7) > rel) ? -INFINITY : s[b][e];
+                for (int hb = 0; hb < 2; ++hb)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            s[rb][hb][b][v] = (32 * hb + 4 * b + v > rel) ? -INFINITY : s[rb][hb][b][v];
+            }
         }
         // row maximum: NaN-propagating maxima need no operand canonicalisation and
         // fold three operands per instruction
         if (need_max) {
-        float mx = s[0][0], mx1 = s[1][0];  // two independent chains
+            need_max = exact;
 #pragma unroll
-        for (int e = 1; e < 16; ++e) {
-            mx = __builtin_elementwise_maximum(mx, s[0][e]);
-            mx1 = __builtin_elementwise_maximum(mx1, s[1][e]);
-        }
-        mx = __builtin_elementwise_maximum(mx, mx1);
-        {
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-            mx = __builtin_elementwise_maximum(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-        }
-        const float m_tile = mx * c;
-        if (__any(m_tile > m_run + kTileLog2Thresh)) {
-            const float m_new = fmaxf(m_run, m_tile);
-            // rows that have seen no visible key yet (all -inf; possible in a key chunk
-            // that starts past them) hold o = l = 0: any finite alpha keeps them so
-            const float alpha = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-            m_run = m_new;
-            l_run *= alpha;
-            l_run1 *= alpha;
+            for (int rb = 0; rb < RB; ++rb) {
+                float mx = s[rb][0][0][0];
 #pragma unroll
-            for (int db = 0; db < DB; ++db) o[db] *= alpha;
-        }
-        need_max = exact || __any(m_run == -INFINITY);
-        neg_off = m_run == -INFINITY ? 0.f : -m_run;
+                for (int e = 1; e < 16; ++e)
+                    mx = __builtin_elementwise_maximum(mx, s[rb][e >> 3][(e >> 2) & 1][e & 3]);
+                {
+                    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+                    mx = __builtin_elementwise_maximum(__uint_as_float(x[0]), __uint_as_float(x[1]));
+                    const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+                    mx = __builtin_elementwise_maximum(__uint_as_float(y[0]), __uint_as_float(y[1]));
+                }
+                const float m_tile = mx * c;
+                if (__any(m_tile > m_run[rb] + kTileLog2Thresh)) {
+                    const float m_new = fmaxf(m_run[rb], m_tile);
+                    // rows that have seen no visible key yet (all -inf; possible in a key chunk
+                    // that starts past them) hold o = l = 0: any finite alpha keeps them so
+                    const float alpha = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[rb] - m_new);
+                    m_run[rb] = m_new;
+                    l_run[rb] *= alpha;
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) o[rb][db] *= alpha;
+                }
+                need_max |= __any(m_run[rb] == -INFINITY);
+                neg_off[rb] = m_run[rb] == -INFINITY ? 0.f : -m_run[rb];
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
 
-        // O^T += V^T . P^T, one 16-key step st at a time: the weights of step st are
-        // computed, then its DB MFMAs are issued with the next step's weights computed
-        // between them, in kParts parts (one after every DB / kParts products), so that
-        // the exponentials of one step overlap the products of the step before. Quarters
-        // for the 8-wavefront bf16 tiles at d = 128, halves otherwise (measured: quarters
-        // 1 % faster than halves on the wide tiles, 1.5 % slower on the 128-row ones).
-        bf16x8 pf[4];
-        constexpr int kParts = (!FP8 && WAVES == 8 && DB >= 4) ? 4 : 2;
-        static_assert(DB % kParts == 0 && 4 % kParts == 0, "weight parts");
-        // part `part` of step st's eight weights, as bf16, and their row sums: pair q of the
-        // step (weights 2q, 2q + 1) goes to l_run for even q and to l_run1 for odd q, in pair
-        // order, so the sums do not depend on kParts
-        auto weights_part = [&](int st, int part) {
-            const int b = st >> 1, e0 = (st & 1) * 8;
-#pragma unroll
-            for (int e = 8 * part / kParts; e < 8 * (part + 1) / kParts; ++e)
-                pf[st][e] = (__bf16)__builtin_amdgcn_exp2f(fmaf(s[b][e0 + e], c, neg_off));
-#pragma unroll
-            for (int q = 4 * part / kParts; q < 4 * (part + 1) / kParts; ++q) {
-                const bf16x2 pq = {pf[st][2 * q], pf[st][2 * q + 1]};
-                if (q % 2 == 0) l_run = __builtin_amdgcn_fdot2_f32_bf16(pq, ones, l_run, false);
-                else l_run1 = __builtin_amdgcn_fdot2_f32_bf16(pq, ones, l_run1, false);
-            }
+        // O^T += V^T . P^T
+        bf16x8 pf[RB][2];
+        // pair q of a half's eight weights of a row, as bf16, and its part of the row sum
+        auto w_pair = [&](int rb, int hb, int q) {
+            const float x0 = s[rb][hb][q >> 1][2 * (q & 1)], x1 = s[rb][hb][q >> 1][2 * (q & 1) + 1];
+            const bf16x2 pq = {(__bf16)__builtin_amdgcn_exp2f(fmaf(x0, c, neg_off[rb])),
+                               (__bf16)__builtin_amdgcn_exp2f(fmaf(x1, c, neg_off[rb]))};
+            pf[rb][hb][2 * q] = pq[0];
+            pf[rb][hb][2 * q + 1] = pq[1];
+            l_run[rb] = __builtin_amdgcn_fdot2_f32_bf16(pq, ones, l_run[rb], false);
             // keep the sums here, beside the products (not sunk to the end of the tile)
-            asm volatile("" : "+v"(l_run), "+v"(l_run1));
+            asm volatile("" : "+v"(l_run[rb]));
         };
+        // The weights are computed in blocks, not between single products: a wavefront's
+        // vector instructions and its own 16-cycle products hardly overlap (about one per
+        // product does), those of the SIMD's other wavefront do. All of a tile's weights
+        // first on the 8-wavefront tiles; on the 4-wavefront ones the first half's, then a
+        // quarter of the second half's after every quarter of the first half's products
+        // (a pair after every fragment: 2 % slower on wide tiles, 10 % on the 8B chat batch).
+        constexpr bool kAllFirst = WAVES == kWideWaves;
 #pragma unroll
-        for (int part = 0; part < kParts; ++part) weights_part(0, part);
+        for (int hb = 0; hb < (kAllFirst ? 2 : 1); ++hb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) w_pair(rb, hb, q);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int st = 0; st < 4; ++st) {
+        for (int i = 0; i < 2 * DB; ++i) {
+            const int hb = i / DB, db = i % DB;
+            if (i + kAhead < 2 * DB) vread(i + kAhead);
 #pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                const int i = st * DB + db;
-                if (i + kAheadV < 4 * DB) vread(i + kAheadV);
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i], pf[st], o[db], 0, 0, 0);
+            for (int rb = 0; rb < RB; ++rb)
+                o[rb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i], pf[rb][hb], o[rb][db], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!kAllFirst && hb == 0 && db % (DB / 4) == DB / 4 - 1) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) w_pair(rb, 1, db / (DB / 4));
                 __builtin_amdgcn_sched_barrier(0);
-                if (st + 1 < 4 && (db + 1) % (DB / kParts) == 0) {
-                    weights_part(st + 1, (db + 1) / (DB / kParts) - 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
             }
         }
     };
@@ -661,7 +717,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         // bf16 pools: the next tile's copies are issued between the first products of
         // this one (piece e after product 3e + 2; 3e + 1 with the append fused in), then
         // the table entries of the tile after
-        static_assert(3 * NI < 2 * DK, "copies fit between the QK^T products");
+        static_assert(3 * NI < 4 * KS, "copies fit between the QK^T products");
         constexpr int kCopyAt = FUSE ? 1 : 2;
         compute_tile(kc, vc, kt, [&](int i) {
             if constexpr (!FP8) {
@@ -690,12 +746,14 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
 
     for (;;) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db) o[db] = f32x16{};
-    m_run = -INFINITY;
-    neg_off = 0.f;
+    for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[rb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m_run[rb] = -INFINITY;
+        neg_off[rb] = 0.f;
+        l_run[rb] = 0.f;
+    }
     need_max = true;
-    l_run = 0.f;
-    l_run1 = 0.f;
     kt = it.kt_begin;
     if (exact) fetch_ids(kt, ids);  // the first pass has them from the start
     if constexpr (FP8) {
@@ -720,15 +778,22 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         step(1);
         if (++kt >= it.kt_end) break;
     }
-    if (exact || !__syncthreads_or(!(l_run + l_run1 <= 0x1p100f))) break;
+    if (exact || !__syncthreads_or(!(l_run[0] <= 0x1p100f) || !(l_run[1] <= 0x1p100f))) break;
     exact = true;
     }
 
-    l_run += l_run1;
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    const float inv = l_tot > 0.f ? a.v_scale / l_tot : 0.f;  // v_scale is 1 for bf16 pools
-    const float lse_v = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : -INFINITY;
-    // o[db][4j + i] is element d = 32db + 8j + 4hh + i of this lane's row
+    float inv[RB], lse_v[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        float l = l_run[rb];
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+        l = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+        const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+        l = __uint_as_float(y[0]) + __uint_as_float(y[1]);
+        inv[rb] = l > 0.f ? a.v_scale / l : 0.f;  // v_scale is 1 for bf16 pools
+        lse_v[rb] = l > 0.f ? (m_run[rb] + log2f(l)) * kLn2 : -INFINITY;
+    }
+    // o[rb][db][v] is element d = 16 db + 4 g4 + v of row 16 rb + j16
     if (it.part < 0) {
         // Output rows go through LDS so that every store writes whole rows: a lane's own
         // values cover 16 bytes of each of 32 rows, 256 bytes apart. The tiles are no
@@ -736,30 +801,33 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         // d = 64) of the tile buffers: its 32 rows, 16-byte chunks XOR-swizzled by row.
         // Each store then covers 256 (128) contiguous bytes of 4 (8) rows, and the rows
         // of one token's query heads are adjacent in the output.
-        constexpr int RB = 2 * D;                       // bytes per row
-        constexpr int CH = RB / 16;                     // 16-byte chunks per row
-        constexpr int kStage = kRowsPerWave * RB;       // bytes per wavefront
+        constexpr int kOutRow = 2 * D;                  // bytes per row
+        constexpr int CH = kOutRow / 16;                // 16-byte chunks per row
+        constexpr int kStage = kRowsPerWave * kOutRow;  // bytes per wavefront
         constexpr int kPerBuf = kTileBytes / kStage;    // wavefronts per tile buffer
         static_assert(kPerBuf * 4 >= WAVES && kPerBuf * kStage == kTileBytes, "stage layout");
         const int sb = wave / kPerBuf;
         unsigned char* stage = (sb == 0 ? k_lds0 : sb == 1 ? v_lds0 : sb == 2 ? k_lds1 : v_lds1) +
                                (wave % kPerBuf) * kStage;
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int rb = 0; rb < RB; ++rb) {
+            const int row = 16 * rb + j16;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
+            for (int db = 0; db < DB; ++db) {
                 u32x2 w;
-                w[0] = pack_bf16x2(o[db][4 * j] * inv, o[db][4 * j + 1] * inv);
-                w[1] = pack_bf16x2(o[db][4 * j + 2] * inv, o[db][4 * j + 3] * inv);
-                *reinterpret_cast<u32x2*>(stage + lr * RB + ((4 * db + j) ^ (lr & (CH - 1))) * 16 + 8 * hh) = w;
+                w[0] = pack_bf16x2(o[rb][db][0] * inv[rb], o[rb][db][1] * inv[rb]);
+                w[1] = pack_bf16x2(o[rb][db][2] * inv[rb], o[rb][db][3] * inv[rb]);
+                *reinterpret_cast<u32x2*>(stage + row * kOutRow + ((2 * db + (g4 >> 1)) ^ (row & (CH - 1))) * 16 +
+                                          8 * (g4 & 1)) = w;
             }
-        if (row_ok && a.lse != nullptr && hh == 0) a.lse[qrow] = lse_v;
+            if (row_ok[rb] && a.lse != nullptr && g4 == 0) a.lse[qrow[rb]] = lse_v[rb];
+        }
         wave_lds_sync();
         constexpr int kRowsPerStore = 64 / CH;
 #pragma unroll
         for (int i = 0; i < kRowsPerWave / kRowsPerStore; ++i) {
             const int rr = i * kRowsPerStore + lane / CH, ch = lane % CH;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(stage + rr * RB + (ch ^ (rr & (CH - 1))) * 16);
+            const u32x4 v = *reinterpret_cast<const u32x4*>(stage + rr * kOutRow + (ch ^ (rr & (CH - 1))) * 16);
             const int mr = wave * kRowsPerWave + rr;  // the stored row's token and head
             const int tr = mr / a.group;
             if (tr < ntok) {
@@ -771,10 +839,10 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         // Partial rows (fp32) of a split item, through the same stage: the wavefront's 32
         // rows are contiguous in the partial buffer, so each store covers whole rows; rows
         // larger than the stage go in rounds of kRows.
-        constexpr int RB = 4 * D;                             // bytes per fp32 row
-        constexpr int CH = RB / 16;                           // 16-byte chunks per row
+        constexpr int kOutRow = 4 * D;                        // bytes per fp32 row
+        constexpr int CH = kOutRow / 16;                      // 16-byte chunks per row
         constexpr int kStage = 4 * kTileBytes / WAVES;        // stage bytes per wavefront
-        constexpr int kRows = kStage / RB < kRowsPerWave ? kStage / RB : kRowsPerWave;
+        constexpr int kRows = kStage / kOutRow < kRowsPerWave ? kStage / kOutRow : kRowsPerWave;
         static_assert(kRows >= 2 && kRowsPerWave % kRows == 0 && (kRows * CH) % 64 == 0, "partial stage");
         constexpr int kPerBuf = kTileBytes / kStage;
         const int sb = wave / kPerBuf;
@@ -784,28 +852,28 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         constexpr int kSw = CH < 16 ? CH : 16;                // chunk swizzle span
 #pragma unroll
         for (int r0 = 0; r0 < kRowsPerWave; r0 += kRows) {
-            if (lr >= r0 && lr < r0 + kRows) {
-                const int sr = lr - r0;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                const int sr = 16 * rb + j16 - r0;
+                if (sr < 0 || sr >= kRows) continue;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        f32x4 w = {o[db][4 * j] * inv, o[db][4 * j + 1] * inv, o[db][4 * j + 2] * inv,
-                                   o[db][4 * j + 3] * inv};
-                        const int ch = (8 * db + 2 * j + hh) ^ (sr & (kSw - 1));
-                        *reinterpret_cast<f32x4*>(stage + sr * RB + ch * 16) = w;
-                    }
+                    *reinterpret_cast<f32x4*>(stage + sr * kOutRow + ((4 * db + g4) ^ (sr & (kSw - 1))) * 16) =
+                        o[rb][db] * inv[rb];
             }
             wave_lds_sync();
 #pragma unroll
             for (int i = 0; i < kRows * CH / 64; ++i) {
                 const int c = i * 64 + lane, sr = c / CH, ch = c % CH;
-                const f32x4 v = *reinterpret_cast<const f32x4*>(stage + sr * RB + (ch ^ (sr & (kSw - 1))) * 16);
+                const f32x4 v = *reinterpret_cast<const f32x4*>(stage + sr * kOutRow + (ch ^ (sr & (kSw - 1))) * 16);
                 *reinterpret_cast<f32x4*>(a.part_o + (prow0 + r0 + sr) * D + ch * 4) = v;
             }
             wave_lds_sync();  // the next round overwrites the stage
         }
-        if (hh == 0) a.part_lse[prow0 + lr] = lse_v;
+        if (g4 == 0) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) a.part_lse[prow0 + 16 * rb + j16] = lse_v[rb];
+        }
     }
 }
 
