@@ -122,19 +122,38 @@ def load_library(path: str | None = None):
     return lib
 
 
+_torch = None
+
+
+def _t():
+    """The torch module (imported on first use; an import statement on every call of these
+    functions is a noticeable part of a small call)."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _check(fn, status, lib):
     if status != GC_OK:
         raise GcError(fn, status, lib)
 
 
 def _stream_handle(stream=None):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _t()
+    # (the raw handle: a Stream object per call takes as long as a kernel launch)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _require(t, dtype, name, device=None):
-    import torch
+    torch = _t()
+    # one test for what every valid call passes, the tests one by one for the others
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.is_contiguous() and
+            (device is None or t.device == device)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -183,7 +202,7 @@ class PagedBatch:
 
     @property
     def total_new(self) -> int:
-        return int(self.new_lens.sum())
+        return int(np.add.reduce(self.new_lens))
 
     @property
     def max_blocks_per_seq(self) -> int:
@@ -200,9 +219,9 @@ def geometry(num_q_heads, num_kv_heads, head_dim, num_blocks, max_blocks_per_seq
 
 def _geo_from_pools(k_pool, v_pool, q_heads, batch: PagedBatch):
     NB, Hkv, S, D = k_pool.shape
-    if tuple(v_pool.shape) != (NB, Hkv, D, S):
+    if v_pool.shape != (NB, Hkv, D, S):
         raise ValueError(f"v_pool must be [NB][Hkv][D][S] = {(NB, Hkv, D, S)}, got {tuple(v_pool.shape)}")
-    return geometry(q_heads, Hkv, D, NB, batch.max_blocks_per_seq, S)
+    return Geometry(int(q_heads), Hkv, D, S, NB, batch.max_blocks_per_seq)
 
 
 def _opts(kv_split_tiles, tiling=None):
@@ -216,7 +235,7 @@ def _opts(kv_split_tiles, tiling=None):
 
 def kv_append(k_new, v_new, k_pool, v_pool, batch: PagedBatch, stream=None):
     """Append the new tokens' K/V ([T][Hkv][D] bf16) into the pools in place."""
-    import torch
+    torch = _t()
     lib = load_library()
     for name, t in (("k_new", k_new), ("v_new", v_new), ("k_pool", k_pool), ("v_pool", v_pool)):
         _require(t, torch.bfloat16, name, batch.device)
@@ -236,7 +255,7 @@ def kv_restore(k_src, v_src, k_pool, v_pool, batch: PagedBatch, stream=None):
     may be pinned host tensors, which the GPU reads directly over PCIe (the cache's
     CPU tier), or device tensors. This is gc_kv_append with prefix lengths 0 and new
     lengths P_r; the restore batch's device arrays are built once per PagedBatch."""
-    import torch
+    torch = _t()
     lib = load_library()
     for name, t in (("k_src", k_src), ("v_src", v_src)):
         if t.dtype != torch.bfloat16 or not t.is_contiguous():
@@ -278,7 +297,7 @@ def alloc_workspace(num_q_heads, k_pool, v_pool, batch: PagedBatch, kv_split_til
 
 
 def _attn_args(q, k_pool, v_pool, batch, out, lse, workspace, pool_dtype=None):
-    import torch
+    torch = _t()
     pool_dtype = pool_dtype or torch.bfloat16
     _require(q, torch.bfloat16, "q", batch.device)
     _require(k_pool, pool_dtype, "k_pool", batch.device)
@@ -290,11 +309,11 @@ def _attn_args(q, k_pool, v_pool, batch, out, lse, workspace, pool_dtype=None):
     if out is None:
         out = torch.empty_like(q)
     _require(out, torch.bfloat16, "out", batch.device)
-    if tuple(out.shape) != tuple(q.shape):
+    if out.shape != q.shape:
         raise ValueError("out must have q's shape")
     if lse is not None:
         _require(lse, torch.float32, "lse", batch.device)
-        if tuple(lse.shape) != (T, Hq):
+        if lse.shape != (T, Hq):
             raise ValueError("lse must be [T][Hq] float32")
     if workspace is not None:
         _require(workspace, torch.uint8, "workspace", batch.device)
@@ -303,7 +322,7 @@ def _attn_args(q, k_pool, v_pool, batch, out, lse, workspace, pool_dtype=None):
 
 def plan(num_q_heads, k_pool, v_pool, batch: PagedBatch, workspace, kv_split_tiles=None, stream=None,
          tiling=None):
-    import torch
+    torch = _t()
     lib = load_library()
     _require(workspace, torch.uint8, "workspace", batch.device)
     geo = _geo_from_pools(k_pool, v_pool, num_q_heads, batch)
@@ -336,7 +355,7 @@ def plan_status(workspace, stream=None) -> int:
     """Status of the last plan in `workspace` (waits for the stream): GC_OK when the
     device lengths agreed with the host's, GC_ERR_LENGTHS when they did not (the plan
     then holds no work). Other failures raise."""
-    import torch
+    torch = _t()
     lib = load_library()
     _require(workspace, torch.uint8, "workspace")
     st = lib.gc_prefix_prefill_plan_status(workspace.data_ptr(), workspace.numel(), _stream_handle(stream))
@@ -360,14 +379,14 @@ def run(q, k_pool, v_pool, batch: PagedBatch, scale, workspace, out=None, lse=No
 
 def run_with_append(q, k_new, v_new, k_pool, v_pool, batch: PagedBatch, scale, workspace, out=None, lse=None,
                     kv_split_tiles=None, stream=None, tiling=None):
-    """Append the new tokens' K/V (bf16 [T][Hkv][D]) into the pools and run the attention,
-    in one launch with prefill tiles, from a plan already in `workspace`."""
-    import torch
+    """Append the new tokens' K/V (bf16 [T][Hkv][D]) into the pools and run the attention
+    from a plan already in `workspace`."""
+    torch = _t()
     lib = load_library()
     geo, out = _attn_args(q, k_pool, v_pool, batch, out, lse, workspace)
     for name, t in (("k_new", k_new), ("v_new", v_new)):
         _require(t, torch.bfloat16, name, batch.device)
-    if tuple(k_new.shape) != (batch.total_new, geo.num_kv_heads, geo.head_dim) or v_new.shape != k_new.shape:
+    if k_new.shape != (batch.total_new, geo.num_kv_heads, geo.head_dim) or v_new.shape != k_new.shape:
         raise ValueError("k_new/v_new must be [T][Hkv][D] matching the batch and pools")
     st = lib.gc_prefix_prefill_run_with_append(
         ctypes.byref(geo), ctypes.byref(batch.desc()), _opts(kv_split_tiles, tiling), q.data_ptr(),
@@ -381,7 +400,7 @@ def run_with_append(q, k_new, v_new, k_pool, v_pool, batch: PagedBatch, scale, w
 def read_bandwidth_probe(buf, sink=None, stream=None):
     """Enqueue one streaming read of every byte of `buf` (a device tensor whose size
     is a multiple of 16 bytes); returns the sink tensor it writes."""
-    import torch
+    torch = _t()
     lib = load_library()
     if not buf.is_cuda or not buf.is_contiguous():
         raise ValueError("buf must be a contiguous device tensor")
@@ -397,7 +416,7 @@ def mfma_peak_probe(iterations, sink=None, device=None, stream=None):
     """Enqueue the matrix-core calibration loop (`iterations` rounds of
     MFMA_PROBE_PRODUCTS_PER_ITERATION bf16 32x32x16 products); returns the sink
     tensor it writes (every entry 4096 * iterations)."""
-    import torch
+    torch = _t()
     lib = load_library()
     if sink is None:
         sink = torch.empty(MFMA_PROBE_SINK_FLOATS, dtype=torch.float32, device=device or "cuda")
@@ -436,7 +455,7 @@ def prefix_prefill_attention(q, k_pool, v_pool, batch: PagedBatch, scale, worksp
 
 def kv_append_fp8(k_new, v_new, k_pool8, v_pool8, batch: PagedBatch, k_scale, v_scale, stream=None):
     """Quantise the new tokens' K/V ([T][Hkv][D] bf16) into the 8-bit pools in place."""
-    import torch
+    torch = _t()
     lib = load_library()
     for name, t in (("k_new", k_new), ("v_new", v_new)):
         _require(t, torch.bfloat16, name, batch.device)
@@ -454,7 +473,7 @@ def kv_append_fp8(k_new, v_new, k_pool8, v_pool8, batch: PagedBatch, k_scale, v_
 
 def run_fp8(q, k_pool8, v_pool8, batch: PagedBatch, scale, k_scale, v_scale, workspace, out=None,
             lse=None, kv_split_tiles=None, stream=None, tiling=None):
-    import torch
+    torch = _t()
     lib = load_library()
     geo, out = _attn_args(q, k_pool8, v_pool8, batch, out, lse, workspace, torch.uint8)
     st = lib.gc_prefix_prefill_run_fp8(ctypes.byref(geo), ctypes.byref(batch.desc()),
@@ -470,7 +489,7 @@ def prefix_prefill_attention_fp8(q, k_pool8, v_pool8, batch: PagedBatch, scale, 
                                  workspace=None, out=None, lse=None, kv_split_tiles=None,
                                  stream=None, tiling=None):
     """prefix_prefill_attention over 8-bit pools (uint8 E4M3 codes, one scale per pool)."""
-    import torch
+    torch = _t()
     lib = load_library()
     if workspace is None:
         workspace = alloc_workspace(q.shape[1], k_pool8, v_pool8, batch, kv_split_tiles, tiling)
@@ -490,7 +509,7 @@ def prepare(k_new, v_new, k_pool, v_pool, batch: PagedBatch, num_q_heads, worksp
             stream=None, tiling=None, k_scale=None, v_scale=None):
     """Append the new tokens' K/V and plan the attention in one launch (then call run
     or run_fp8 with the same options). 8-bit pools (uint8) take k_scale and v_scale."""
-    import torch
+    torch = _t()
     lib = load_library()
     fp8 = k_pool.dtype == torch.uint8
     for name, t in (("k_new", k_new), ("v_new", v_new)):
