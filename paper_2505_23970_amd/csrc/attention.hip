@@ -2,7 +2,7 @@
 // attention_kernels.h). This file is compiled with the scheduler's
 // register-pressure trackers enabled (the flags in build.py): measured on the
 // bf16 kernels, 0.4-0.9 % faster on the compute-bound workloads and neutral on
-// the others. The 8-bit-pool, fused-append and merge kernels are launched from
+// the others. The 8-bit-pool and merge kernels are launched from
 // attention_plain.hip, built without that option (the 8-bit 128-row kernel was
 // 2 % slower with it).
 #include "attention_kernels.h"

@@ -69,23 +69,12 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 
 
-// A direct global->LDS copy of 16 bytes per lane: lane i's bytes land at
-// lds_dst + 16 i (lds_dst is wave-uniform). Issued as inline assembly so the
-// compiler does not track it: every wait for these copies is explicit (wait_vmem).
-// The compiler emits no other use of m0 in these kernels; the clobber keeps it that way.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(const void* gsrc, const unsigned char* lds_dst) {
-    const uint32_t l = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)lds_dst);
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :: "v"(gsrc), "s"(l) : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-// The same with a wave-uniform base (scalar registers), a 32-bit lane offset and the LDS
-// byte address already at hand: the four copies of a tile and wavefront then cost no
-// vector instruction besides themselves, where the 64-bit lane addresses took an addition
+// A direct global->LDS copy of 16 bytes per lane, from base + off (a wave-uniform base in
+// scalar registers, a 32-bit lane offset): lane i's bytes land at lds + 16 i (a wave-uniform
+// LDS byte address). Issued as inline assembly so the compiler does not track it: every
+// wait for these copies is explicit (wait_vmem). The compiler emits no other use of m0 in
+// these kernels; the clobber keeps it that way. The four copies of a tile and wavefront cost
+// no vector instruction besides themselves, where 64-bit lane addresses took an addition
 // each between the QK^T products (mixed 70B batch 2223 -> 2206 us with the offset and the
 // first-tile test kept out of the tile loop, 32k reuse 489 -> 483, 8B chat 132.7 -> 128.6).
 #pragma clang diagnostic push
@@ -132,13 +121,10 @@ __device__ __forceinline__ void widen_e4m3x16(const u32x4 c, u32x4& lo, u32x4& h
     hi = u32x4{w[4], w[5], w[6], w[7]};
 }
 
-// One work item (a workgroup of WAVES wavefronts): the item of launch index bid
-// (blockIdx.x in the regular launch), i.e. work item bid / Hkv for KV head bid % Hkv. FUSE: the KV append runs in the
-// same launch, so the keys at or past the prefix length are taken from the new
-// tokens' arrays, not from the pool (bf16 pools only).
-template <int D, int WAVES, bool FP8, bool FUSE>
+// One work item (a workgroup of WAVES wavefronts): the item of launch index bid (blockIdx.x
+// in the regular launch), i.e. work item bid / Hkv for KV head bid % Hkv.
+template <int D, int WAVES, bool FP8>
 __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned bid) {
-    static_assert(!(FP8 && FUSE), "the fused append runs over bf16 pools");
     constexpr int kBlockRows = WAVES * kRowsPerWave;  // query rows of a work item
     constexpr int KS = D / 32;                      // k-steps of QK^T
     constexpr int DB = D / 16;                      // 16-row blocks of O^T
@@ -246,64 +232,29 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     const int32_t* table = a.block_tables + (int64_t)r * a.max_blocks;
     const int64_t head_off = (int64_t)kvh * kPageBytes;
     const int64_t block_stride = (int64_t)a.num_kv_heads * kPageBytes;
-    // fused append: this KV head's rows of the request's new tokens (new key P + i at
-    // row i) and the byte stride between consecutive tokens
-    const int64_t new_stride = (int64_t)a.num_kv_heads * D * 2;
-    auto new_rows = [&](const uint16_t* base) {
-        return reinterpret_cast<const unsigned char*>(base) + ((int64_t)cu * a.num_kv_heads + kvh) * D * 2;
-    };
-    const unsigned char* k_new_h = FUSE ? new_rows(a.k_new) : nullptr;
-    // the values as a buffer of exactly these rows' bytes (the host keeps them < 2 GiB)
-    const __amdgpu_buffer_rsrc_t v_new_r = __builtin_amdgcn_make_buffer_rsrc(
-        FUSE ? (void*)new_rows(a.v_new) : nullptr, (short)0,
-        FUSE ? (int)((int64_t)max(n - 1, 0) * new_stride + 2 * D) : 0, kBufferFlags);
-
     // raw table entries of tile kt (indices clamped into the row; checked at use)
     // (a vector load: lane p of every 4 holds entry p; it completes with the tile loads,
     // and no scalar load is left in flight to force full LDS waits in the compute phase)
     auto fetch_ids = [&](int kt, int& ids) {
         ids = table[(uint32_t)min(kt * 4 + (lane & 3), a.max_blocks - 1)];
     };
-    // Copies of piece e of tile kt (one page of K and of V for this wave). Plain
-    // attention: a page past the table, past the sequence or with a block id outside
-    // the pool is copied from block 0 instead (its keys are masked and its values
-    // zeroed after the copy), so the copy needs no branch and can be issued between
-    // the products of the tile before. Fused append: pages that are not copied are
-    // skipped, and a page of new keys takes its values from registers.
+    // Copies of piece e of tile kt (one page of K and of V for this wave). A page past the
+    // table, past the sequence or with a block id outside the pool is copied from block 0
+    // instead (its keys are masked and its values zeroed after the copy), so the copy needs
+    // no branch and can be issued between the products of the tile before.
     // (blk: the raw table entry of the page, read from the lanes of `ids` beforehand)
     // (the destination: buffer 0 or 1 of the tiles)
     const uint32_t lds_piece = __builtin_amdgcn_readfirstlane(sub * 1024);
     const unsigned char* kpool = reinterpret_cast<const unsigned char*>(a.k_pool);
     const unsigned char* vpool = reinterpret_cast<const unsigned char*>(a.v_pool);
-    // plain attention: byte offset in the pools of the page that piece e of tile kt copies
-    auto page_offset = [&](int kt, const int blk, int e) -> int64_t {
-        const int lp = kt * 4 + page_of(e);
-        const bool ok = lp < a.max_blocks && lp * kPage < L && blk >= 0 && blk < a.num_blocks;
-        return (int64_t)(ok ? blk : 0) * block_stride + head_off;
-    };
-    auto issue_plain = [&](int buf, const int64_t off, int e) {
-        const uint32_t at = page_of(e) * kPageBytes + lds_piece;
-        dma16(kpool + off, k_src[e & 1], lds_address(buf ? k_lds1 : k_lds0) + at);
-        dma16(vpool + off, v_src, lds_address(buf ? v_lds1 : v_lds0) + at);
-    };
     auto issue_page = [&](int buf, int kt, const int blk, int e) {
-        unsigned char* kdst = buf ? k_lds1 : k_lds0;
-        unsigned char* vdst = buf ? v_lds1 : v_lds0;
         const int pg = page_of(e);
         const int lp = kt * 4 + pg;
         const bool ok = lp < a.max_blocks && lp * kPage < L && blk >= 0 && blk < a.num_blocks;
-        if constexpr (!FUSE) {
-            issue_plain(buf, page_offset(kt, blk, e), e);
-        } else if (ok) {
-            const int64_t base = (int64_t)blk * block_stride + head_off;
-            const unsigned char* ks = kpool + base + k_src[e & 1];
-            if (lp * kPage + kPage > P) {           // the page holds new keys
-                const int pos = lp * kPage + k_row;  // this lane's key
-                if (pos >= P && pos < L) ks = k_new_h + (int64_t)(pos - P) * new_stride + k_chunk(e);
-            }
-            dma16(ks, kdst + pg * kPageBytes + sub * 1024);
-            if (lp * kPage < P) dma16(vpool + base + v_src, vdst + pg * kPageBytes + sub * 1024);
-        }
+        const int64_t off = (int64_t)(ok ? blk : 0) * block_stride + head_off;
+        const uint32_t at = pg * kPageBytes + lds_piece;
+        dma16(kpool + off, k_src[e & 1], lds_address(buf ? k_lds1 : k_lds0) + at);
+        dma16(vpool + off, v_src, lds_address(buf ? v_lds1 : v_lds0) + at);
     };
     auto page_ids = [&](const int ids, int (&blk)[NI]) {
 #pragma unroll
@@ -328,70 +279,6 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
 #pragma unroll
             for (int x = 0; x < 8; ++x)
                 if (key0 + x >= first_bad) dst[x] = 0;
-        }
-    };
-
-    // Fused append, values of new keys. Their rows are token-major, the LDS tile is
-    // transposed, so they go through registers: the lanes of a wavefront cover exactly
-    // the 1 KiB pieces its own copies fill (32 value rows x 16 keys of one page), one
-    // (8 keys, 2 value rows) task per lane and pass: eight 4-byte loads issued with the
-    // tile's copies and held during the previous tile's products, then two 16-byte
-    // LDS writes (element writes in the group that holds the first new key, whose
-    // prefix keys come from the pool). The loads go through a buffer resource over the
-    // request's rows, so a key before the prefix end (negative offset) or at or past
-    // the sequence end reads as 0 without a test; a tile's offsets stay within
-    // (-64, n) rows of the first new key.
-    constexpr int kNewTasks = 32 * NI;  // per wavefront and tile
-    constexpr int NV = FUSE ? (kNewTasks + 63) / 64 : 1;
-    uint32_t nv[NV][8];
-    auto has_new = [&](int kt) { return kt * kBlockN + kBlockN > P; };
-    auto task_of = [&](int j, int& pg, int& d0, int& half) {
-        const int t = lane + 64 * j;
-        pg = page_of(t >> 5);
-        d0 = 32 * sub + 2 * (t & 15);
-        half = (t >> 4) & 1;
-        return t < kNewTasks;
-    };
-    auto load_newv = [&](int kt) {
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            int pg, d0, half;
-            const bool ok = task_of(j, pg, d0, half);
-            const int key0 = kt * kBlockN + pg * kPage + half * 8;
-            const int stride = (int)new_stride;
-            const int off = ok ? (key0 - P) * stride + d0 * 2 : INT32_MIN / 2;  // lanes without a task read 0
-#pragma unroll
-            for (int x = 0; x < 8; ++x) nv[j][x] = __builtin_amdgcn_raw_buffer_load_b32(v_new_r, off + x * stride, 0, 0);
-        }
-    };
-    auto store_newv = [&](unsigned char* vdst, int kt) {
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            int pg, d0, half;
-            if (!task_of(j, pg, d0, half)) continue;
-            const int key0 = kt * kBlockN + pg * kPage + half * 8;
-            if (key0 + 8 <= P) continue;  // eight prefix keys: the page copy holds them
-            u32x4 r0, r1;                 // rows d0 and d0 + 1 of the eight keys
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                r0[i] = (nv[j][2 * i] & 0xFFFFu) | (nv[j][2 * i + 1] << 16);
-                r1[i] = (nv[j][2 * i] >> 16) | (nv[j][2 * i + 1] & 0xFFFF0000u);
-            }
-            // d0 is even, so rows d0 and d0 + 1 share the half swap
-            unsigned char* row = vdst + pg * kPageBytes + d0 * 32 + ((half ^ ((d0 >> 3) & 1)) * 16);
-            if (key0 >= P) {
-                *reinterpret_cast<u32x4*>(row) = r0;
-                *reinterpret_cast<u32x4*>(row + 32) = r1;
-            } else {
-                uint16_t* w0 = reinterpret_cast<uint16_t*>(row);
-                uint16_t* w1 = reinterpret_cast<uint16_t*>(row + 32);
-#pragma unroll
-                for (int x = 0; x < 8; ++x)
-                    if (key0 + x >= P) {
-                        w0[x] = (uint16_t)(nv[j][x] & 0xFFFFu);
-                        w1[x] = (uint16_t)(nv[j][x] >> 16);
-                    }
-            }
         }
     };
 
@@ -634,64 +521,9 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         }
     };
 
-    // Fused append, pool writes: the keys and values of this work item's own tokens
-    // (positions P + q0 .. P + q0 + ntok - 1) go from the LDS tile that holds them to
-    // their pool slots, bit for bit. Each (token, KV head) has exactly one writer: the
-    // query tile that owns the token, in the key chunk that covers its position. bl
-    // holds the raw block-table entries of tile kt's four pages (wave-uniform); pages
-    // past the table or with a bad id are skipped, as the plain append does.
-    auto write_own = [&](const unsigned char* kb, const unsigned char* vb, int kt, const int (&bl)[4]) {
-        const int lo = max(P + it.q0, kt * kBlockN), hi = min(P + it.q0 + ntok, kt * kBlockN + kBlockN);
-        if (lo >= hi) return;
-        constexpr int CPR = D / 8;  // 16-byte chunks per key row
-        constexpr int THREADS = WAVES * 64;
-        const int64_t page_elems = (int64_t)kPage * D;  // elements of one (block, KV head) page
-        int blk4[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-            blk4[p] = (kt * 4 + p < a.max_blocks && bl[p] >= 0 && bl[p] < a.num_blocks) ? bl[p] : -1;
-        auto page_block = [&](int key) {
-            const int p = key / kPage - kt * 4;
-            return p == 0 ? blk4[0] : p == 1 ? blk4[1] : p == 2 ? blk4[2] : blk4[3];
-        };
-        for (int u = tid; u < (hi - lo) * CPR; u += THREADS) {
-            const int key = lo + u / CPR, c = u % CPR;
-            const int b = page_block(key);
-            if (b < 0) continue;
-            const int rt = key - kt * kBlockN;  // row in the tile
-            const u32x4 v = *reinterpret_cast<const u32x4*>(kb + rt * (2 * D) + swz_k<D>(c, rt) * 16);
-            *reinterpret_cast<u32x4*>(a.k_dst + ((int64_t)b * a.num_kv_heads + kvh) * page_elems +
-                                      (key % kPage) * D + c * 8) = v;
-        }
-        // values: (page, row d, half h) units of 8 slots
-        const int p0 = lo / kPage, np = (hi - 1) / kPage - p0 + 1;
-        for (int u = tid; u < np * 2 * D; u += THREADS) {
-            const int lp = p0 + u / (2 * D), d = (u % (2 * D)) >> 1, h = u & 1;
-            const int k0 = lp * kPage + 8 * h;
-            const int a0 = max(k0, lo), a1 = min(k0 + 8, hi);
-            if (a0 >= a1) continue;
-            const int b = page_block(k0);
-            if (b < 0) continue;
-            const unsigned char* src = vb + (lp - kt * 4) * kPageBytes + d * 32 + ((h ^ ((d >> 3) & 1)) * 16);
-            uint16_t* dst = a.v_dst + ((int64_t)b * a.num_kv_heads + kvh) * page_elems + d * kPage + 8 * h;
-            if (a1 - a0 == 8) {
-                *reinterpret_cast<u32x4*>(dst) = *reinterpret_cast<const u32x4*>(src);
-            } else {
-                const uint16_t* s16 = reinterpret_cast<const uint16_t*>(src);
-                for (int x = 0; x < 8; ++x)
-                    if (k0 + x >= a0 && k0 + x < a1) dst[x] = s16[x];
-            }
-        }
-    };
-
     // One pipeline step: start the next tile's loads into the other buffers, compute
     // this tile, make the next tile visible.
     // (ids: block-table entries of the next tile to copy, entry p in lanes with lane % 4 == p)
-    int bl_cur[4];  // (fused append) the entries of the tile being computed, wave-uniform
-    auto take_ids = [&](int (&bl)[4]) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p) bl[p] = __builtin_amdgcn_readlane(ids, p);
-    };
     int kt = it.kt_begin;
     auto step = [&](const int cur) {  // (cur: the buffer that holds tile kt)
         unsigned char* const kc = cur ? k_lds1 : k_lds0;
@@ -699,8 +531,6 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         unsigned char* const kn = cur ? k_lds0 : k_lds1;
         unsigned char* const vn = cur ? v_lds0 : v_lds1;
         const bool more = kt + 1 < it.kt_end;
-        int bl_next[4];
-        if constexpr (FUSE) take_ids(bl_next);
         // the next tile's block ids, read before any copy of this step is in flight (the
         // compiler waits for every outstanding load before reading `ids`)
         int nb[NI];
@@ -710,15 +540,12 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
                 load8(kt + 1, ids);
                 if (kt + 2 < it.kt_end) fetch_ids(kt + 2, ids);
             }
-            if constexpr (FUSE)
-                if (has_new(kt + 1)) load_newv(kt + 1);
         }
-        if constexpr (FUSE) write_own(kc, vc, kt, bl_cur);
         // bf16 pools: the next tile's copies are issued between the first products of
-        // this one (piece e after product 3e + 2; 3e + 1 with the append fused in), then
-        // the table entries of the tile after
+        // this one (piece e after those of K fragment 3e + 2), then the table
+        // entries of the tile after
         static_assert(3 * NI < 4 * KS, "copies fit between the QK^T products");
-        constexpr int kCopyAt = FUSE ? 1 : 2;
+        constexpr int kCopyAt = 2;
         compute_tile(kc, vc, kt, [&](int i) {
             if constexpr (!FP8) {
                 if (i % 3 == kCopyAt && i / 3 < NI) {
@@ -733,15 +560,10 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
                 store8(kn, vn, kt + 1);
             } else {
                 wait_vmem<0>();
-                if constexpr (FUSE)
-                    if (has_new(kt + 1)) store_newv(vn, kt + 1);
                 zero_tail(vn, kt + 1);
             }
         }
         __syncthreads();
-        if constexpr (FUSE)
-#pragma unroll
-            for (int p = 0; p < 4; ++p) bl_cur[p] = bl_next[p];
     };
 
     for (;;) {
@@ -762,13 +584,8 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         store8(k_lds0, v_lds0, kt);
     } else {
         issue_tile(0, kt, ids);
-        if constexpr (FUSE) take_ids(bl_cur);
-        if constexpr (FUSE)
-            if (has_new(kt)) load_newv(kt);
         if (kt + 1 < it.kt_end) fetch_ids(kt + 1, ids);
         wait_vmem<0>();
-        if constexpr (FUSE)
-            if (has_new(kt)) store_newv(v_lds0, kt);
         zero_tail(v_lds0, kt);
     }
     __syncthreads();
@@ -879,15 +696,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
 
 template <int D, int WAVES, bool FP8>
 __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void attention_kernel(const AttnArgs a) {
-    attention_body<D, WAVES, FP8, false>(a, blockIdx.x);
-}
-
-// Attention with the KV append fused in: the work items read new keys from the new
-// tokens' arrays (so they do not wait for any append) and write their own tokens'
-// keys and values into the pools from LDS.
-template <int D, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void attention_append_kernel(const AttnArgs a) {
-    attention_body<D, WAVES, false, true>(a, blockIdx.x);
+    attention_body<D, WAVES, FP8>(a, blockIdx.x);
 }
 
 // Resident launch (wide tiles): one workgroup per compute unit, each
@@ -923,7 +732,7 @@ __global__ __launch_bounds__(kWideWaves * 64, 1) void attention_resident_kernel(
         const int b = s_tk;
         __syncthreads();  // every wavefront has read the ticket before the next one is written
         if (b < 0) break;
-        attention_body<D, kWideWaves, FP8, false>(a, (unsigned)b);
+        attention_body<D, kWideWaves, FP8>(a, (unsigned)b);
     }
     if (threadIdx.x == 0) {
         const int out = __hip_atomic_fetch_add(&a.queues[kQueues], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

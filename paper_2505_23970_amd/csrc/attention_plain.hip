@@ -1,6 +1,5 @@
-// Launchers of the attention kernels over 8-bit pools, of the attention kernels
-// with the KV append fused in, and of the split merge (the kernels are in
-// attention_kernels.h), built with the compiler's default scheduling.
+// Launchers of the attention kernels over 8-bit pools and of the split merge (the
+// kernels are in attention_kernels.h), built with the compiler's default scheduling.
 #include "attention_kernels.h"
 
 namespace gc {
@@ -27,23 +26,6 @@ hipError_t launch_attention_fp8(const AttnArgs& a, int head_dim, int64_t num_ite
             attention_kernel<128, kWaves, true><<<grid, kWaves * 64, 0, s>>>(a);
         else
             attention_kernel<64, kWaves, true><<<grid, kWaves * 64, 0, s>>>(a);
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_attention_append(const AttnArgs& a, int head_dim, int64_t num_items, bool wide,
-                                   hipStream_t s) {
-    const dim3 grid((unsigned)(num_items * a.num_kv_heads));
-    if (wide) {
-        if (head_dim == 128)
-            attention_append_kernel<128, kWideWaves><<<grid, kWideWaves * 64, 0, s>>>(a);
-        else
-            attention_append_kernel<64, kWideWaves><<<grid, kWideWaves * 64, 0, s>>>(a);
-    } else {
-        if (head_dim == 128)
-            attention_append_kernel<128, kWaves><<<grid, kWaves * 64, 0, s>>>(a);
-        else
-            attention_append_kernel<64, kWaves><<<grid, kWaves * 64, 0, s>>>(a);
     }
     return hipGetLastError();
 }
