@@ -28,6 +28,7 @@ struct Plan {
     int64_t items = 0, combines = 0, partials = 0;
     int max_splits = 1;  // key chunks of the query tile with the most
     int group_cost = gc::kCostBuckets;  // work-list order (gc::PlanArgs)
+    int buckets = gc::kCostBuckets;
     gc::WorkspaceLayout layout{};
 };
 
@@ -243,6 +244,7 @@ gc_status make_plan(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
                     const gc_plan_options* o, Plan* pl) {
     pl->chunk = choose_chunk(geo, b, sh, o);
     pl->items = pl->combines = pl->partials = 0;
+    int longest = 0;  // key tiles of the longest request
     for (int r = 0; r < b->batch; ++r) {
         const int P = b->prefix_lens_host[r], n = b->new_lens_host[r];
         const RequestCounts c = gc::request_counts(P, n, sh.tq, pl->chunk, sh.block_n);
@@ -250,7 +252,9 @@ gc_status make_plan(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
         pl->combines += c.combines;
         pl->partials += c.partials;
         if (n > 0) {  // a request's last query tile sees the most keys
-            const int ns = gc::num_splits(gc::ceil_div(P + n, sh.block_n), pl->chunk);
+            const int kt = gc::ceil_div(P + n, sh.block_n);
+            if (kt > longest) longest = kt;
+            const int ns = gc::num_splits(kt, pl->chunk);
             if (ns > pl->max_splits) pl->max_splits = ns;
         }
     }
@@ -258,6 +262,10 @@ gc_status make_plan(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
     pl->layout = gc::workspace_layout(b->batch, pl->items, pl->combines, pl->partials,
                                       geo->num_kv_heads, geo->head_dim, sh.block_m);
     choose_order(geo, b, sh, pl);
+    // the largest sort key: a request's key tiles where items are grouped, an item's otherwise
+    int key = pl->group_cost < gc::kCostBuckets || pl->chunk <= 0 || longest < pl->chunk ? longest : pl->chunk;
+    if (key > gc::kCostBuckets - 1) key = gc::kCostBuckets - 1;
+    pl->buckets = (key / gc::kPlanThreads + 1) * gc::kPlanThreads;
     return GC_OK;
 }
 
@@ -300,6 +308,7 @@ gc::PlanArgs plan_args(const gc_geometry* geo, const gc_batch* b, const Shape& s
     a.total_tokens = (int32_t)sh.total_tokens;
     a.max_blocks = geo->max_blocks_per_seq;
     a.group_cost = pl.group_cost;
+    a.buckets = pl.buckets;
     return a;
 }
 

@@ -68,11 +68,6 @@ __host__ __device__ inline int num_splits(int kt, int chunk) {
     return (chunk <= 0 || kt <= chunk) ? 1 : ceil_div(kt, chunk);
 }
 
-// first key tile of chunk s out of ns (balanced; every chunk non-empty when ns <= kt)
-__host__ __device__ inline int split_begin(int s, int kt, int ns) {
-    return (int)(((int64_t)s * kt) / ns);
-}
-
 // Pool pages that receive new tokens over the batch (the append grid), from the
 // host lengths: pages P_r / 16 .. (P_r + n_r - 1) / 16 of every request with n_r > 0.
 inline int64_t append_pages_host(const int32_t* prefix, const int32_t* n, int batch) {
@@ -169,6 +164,10 @@ struct PlanArgs {
     // tiles (so the items of one request stay together), lighter ones by their own
     // cost; kCostBuckets gives the plain cost order.
     int32_t group_cost;
+    // Buckets of the counting sort that this batch can use: more than its largest sort
+    // key, a multiple of kPlanThreads, at most kCostBuckets (clearing and scanning all
+    // 2048 for a batch of short chunks took 0.5-1 of the plan's 5-12 us).
+    int32_t buckets;
 };
 
 struct AttnArgs {

@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kAppendThreads) void prepare_kernel(const AppendArg
 }  // namespace
 
 hipError_t launch_prepare(const AppendArgs& aa, const PlanArgs& pa, int head_dim, bool fp8, hipStream_t s) {
-    const dim3 grid((unsigned)(1 + (int64_t)aa.total_pages * aa.num_kv_heads));
+    const dim3 grid((unsigned)(1 + (int64_t)aa.total_pages * ceil_div(aa.num_kv_heads, append_heads(head_dim))));
     if (fp8) {
         if (head_dim == 128)
             prepare_kernel<128, true><<<grid, kAppendThreads, 0, s>>>(aa, pa);
