@@ -169,8 +169,9 @@ def auto_kernel_name(w, cus, fp8):
     """Kernel the library's automatic tiling picks for w, named as in the kernel trace
     (the rule of choose_tiling and resident_workgroups in the C ABI, restated: small
     tiles when every request has n * g <= 16, else at d = 128 wide tiles when 256-row tiles are
-    >= 85 % full and their grid is not between one and two per compute unit, run as a
-    resident launch from two rounds of work items on, else 128-row tiles)."""
+    >= 85 % full and either two or more per compute unit or at most one with two key tiles
+    per compute unit, run as a resident launch from two rounds of work items on, else
+    128-row tiles)."""
     g = w.num_q_heads // w.num_kv_heads
     D = w.head_dim
     f = "true" if fp8 else "false"
@@ -181,7 +182,10 @@ def auto_kernel_name(w, cus, fp8):
     units = int(sum((int(n) + tq - 1) // tq for n in w.new_lens))
     rows = int(w.new_lens.sum()) * g
     grid = units * w.num_kv_heads
-    wide = D == 128 and rows * 100 >= units * 256 * 85 and not (cus < grid < 2 * cus)
+    tiles = w.num_kv_heads * sum((int(P) + min(int(n), q0 + tq) + 63) // 64
+                                 for P, n in zip(w.prefix_lens, w.new_lens) for q0 in range(0, int(n), tq))
+    wide = D == 128 and rows * 100 >= units * 256 * 85 and (
+        grid >= 2 * cus or (grid <= cus and tiles >= 2 * cus))
     if wide and cus % 8 == 0 and wide_items(w, cus) * w.num_kv_heads >= 2 * cus:
         # resident launch: one workgroup per CU taking the items from per-XCD queues
         return f"attention_resident_kernel<{D}, {f}>" + split

@@ -25,15 +25,6 @@ HIPCC_FLAGS = [
     # keep the compiler from forming packed fp32 arithmetic
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
-# Extra flags per source file. attention.hip holds the bf16-pool attention
-# kernels, which schedule better with the AMDGPU register-pressure trackers
-# (0.4-0.9 % faster on the compute-bound workloads, neutral on the others); the
-# 8-bit-pool kernels were 2 % slower with them and build from attention_plain.hip
-# without.
-FILE_FLAGS = {
-    "attention.hip": ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"],
-}
-
 
 CONTROL_LIBRARY = os.path.join(HERE, "libgreencache_ctl.so")
 # IEEE double without contraction: the replacement scores are compared exactly
@@ -70,7 +61,7 @@ def _run(cmd, verbose):
 
 
 def build(out: str = LIBRARY, extra=(), verbose=False) -> str:
-    """Compile every source to an object (with its FILE_FLAGS; in parallel), then
+    """Compile every source to an object (in parallel), then
     link the shared library; always from scratch."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = out + f".tmp{os.getpid()}"
@@ -78,7 +69,7 @@ def build(out: str = LIBRARY, extra=(), verbose=False) -> str:
         jobs = []
         for src in sources():
             obj = os.path.join(objdir, os.path.basename(src) + ".o")
-            jobs.append(([hipcc, *HIPCC_FLAGS, *FILE_FLAGS.get(os.path.basename(src), ()), *extra,
+            jobs.append(([hipcc, *HIPCC_FLAGS, *extra,
                           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c", src, "-o", obj], obj))
         workers = max(1, min(len(jobs), os.cpu_count() or 1, 8))
         with concurrent.futures.ThreadPoolExecutor(workers) as pool:

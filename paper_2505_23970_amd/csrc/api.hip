@@ -87,16 +87,24 @@ gc_status check_options(const gc_plan_options* o) {
     return GC_OK;
 }
 
-// Tiling: small tiles (one wavefront per 16 query rows, keys read straight from
-// global memory) when every request's new tokens fit one such tile, which is the
-// decode case. Otherwise LDS-staged prefill tiles: wide ones (256 rows, 8
-// wavefronts, one workgroup per CU) when they would be at least 85 % full and
-// their count is not between one and two per CU (whole units there would leave
-// the last round of workgroups mostly idle, and below one per CU the keys are
-// split into equal chunks); 128-row tiles otherwise. Wide tiles save copies, which is
-// not what bounds d = 64 (half the products for the same weights: the vector unit);
-// three 128-row workgroups share a compute unit there (164 registers) and overlap better:
-// 16 misses of 100 to 1500 tokens 120 us against 148 on wide tiles.
+// Tiling: small tiles (one wavefront per 16 query rows, K and V pages streamed through
+// its own LDS ring) when every request's new tokens fit one such tile, which is the
+// decode case. Otherwise LDS-staged prefill tiles, 128 rows (two workgroups per CU) or
+// wide (256 rows, one workgroup per CU). Wide tiles copy each K/V tile once for twice the
+// rows; over 8-bit pools, which share their plans with bf16 ones, they also widen it once for
+// twice the rows. So at d = 128 and with wide tiles >= 85 % full they are taken, except
+//   - between one and two per CU, where whole units leave the last round mostly idle (bf16,
+//     128-row against wide: 965 us / 1072 at 288 wide tiles);
+//   - below one per CU with fewer than kWideSplitTiles key tiles per CU: a wide launch that
+//     short is one prologue, and two small workgroups cover each other's (20.2 / 23.6 at
+//     1.4 tiles, 20.0 / 23.8 at 1.7; over 8-bit pools 24.9 / 25.7 and 24.2 / 25.3; at 2.5
+//     22.0 / 23.9, but 26.4 / 25.4 over 8-bit pools).
+// Above two per CU, 128-row tiles win over bf16 pools up to about 140 key tiles per CU (79 / 93
+// at 19, 182 / 189 at 85) and lose 2 to 16 % over 8-bit pools at every size, so wide.
+// Not at d = 64 (half the products for the same weights: the vector unit bounds it, not
+// the copies); three 128-row workgroups share a compute unit there (164 registers) and
+// overlap better: 16 misses of 100 to 1500 tokens 120 us against 148 on wide tiles.
+constexpr int kWideSplitTiles = 2;
 int device_cus();
 
 gc_status choose_tiling(const gc_geometry* geo, const gc_batch* b, const gc_plan_options* o, Shape* sh) {
@@ -115,14 +123,20 @@ gc_status choose_tiling(const gc_geometry* geo, const gc_batch* b, const gc_plan
         }
         if (!small && geo->head_dim == 128) {
             const int tq = gc::tokens_per_tile(sh->group, gc::kWideM);
-            int64_t units = 0, rows = 0;
+            int64_t units = 0, rows = 0, tiles = 0;
             for (int r = 0; r < b->batch; ++r) {
-                units += (b->new_lens_host[r] + tq - 1) / tq;
-                rows += (int64_t)b->new_lens_host[r] * sh->group;
+                const int P = b->prefix_lens_host[r], n = b->new_lens_host[r];
+                rows += (int64_t)n * sh->group;
+                for (int q0 = 0; q0 < n; q0 += tq) {
+                    units += 1;
+                    tiles += gc::key_tiles(P, q0, n - q0 < tq ? n - q0 : tq, gc::kBlockN);
+                }
             }
             const int64_t cus = device_cus();
             const int64_t grid = units * geo->num_kv_heads;
-            wide = rows * 100 >= units * gc::kWideM * 85 && !(grid > cus && grid < 2 * cus);
+            tiles *= geo->num_kv_heads;
+            wide = rows * 100 >= units * gc::kWideM * 85 &&
+                   (grid >= 2 * cus || (grid <= cus && tiles >= kWideSplitTiles * cus));
         }
     }
     sh->small = small;

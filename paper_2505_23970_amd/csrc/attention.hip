@@ -1,10 +1,6 @@
 // Launchers of the attention kernels over bf16 pools (the kernels are in
-// attention_kernels.h). This file is compiled with the scheduler's
-// register-pressure trackers enabled (the flags in build.py): measured on the
-// bf16 kernels, 0.4-0.9 % faster on the compute-bound workloads and neutral on
-// the others. The 8-bit-pool and merge kernels are launched from
-// attention_plain.hip, built without that option (the 8-bit 128-row kernel was
-// 2 % slower with it).
+// attention_kernels.h). The 8-bit-pool and merge kernels are launched from
+// attention_plain.hip, so that the two sets compile side by side.
 #include "attention_kernels.h"
 
 namespace gc {
