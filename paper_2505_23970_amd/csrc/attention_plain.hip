@@ -1,5 +1,5 @@
 // Launchers of the attention kernels over 8-bit pools and of the split merge (the
-// kernels are in attention_kernels.h), built with the compiler's default scheduling.
+// kernels are in attention_kernels.h).
 #include "attention_kernels.h"
 
 namespace gc {
