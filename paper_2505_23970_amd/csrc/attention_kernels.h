@@ -608,7 +608,8 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
         const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
         l = __uint_as_float(y[0]) + __uint_as_float(y[1]);
         inv[rb] = l > 0.f ? a.v_scale / l : 0.f;  // v_scale is 1 for bf16 pools
-        lse_v[rb] = l > 0.f ? (m_run[rb] + log2f(l)) * kLn2 : -INFINITY;
+        // (a split item passes a NaN sum on to the merge)
+        lse_v[rb] = l > 0.f ? (m_run[rb] + log2f(l)) * kLn2 : (it.part >= 0 && l != l ? l : -INFINITY);
     }
     // o[rb][db][v] is element d = 16 db + 4 g4 + v of row 16 rb + j16
     if (it.part < 0) {
@@ -789,6 +790,9 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const CombineA
                 const int64_t pr = row0 + (int64_t)(ok ? s0 + u * S : s0) * split_stride;
                 l[u] = ok ? a.part_lse[pr] : -INFINITY;
                 v[u] = *reinterpret_cast<const f32x4*>(a.part_o + pr * D + 4 * c4);
+                // (a padding entry adds weight 0 times 0: the row it read may hold infinities)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) v[u][x] = ok ? v[u][x] : 0.f;
             }
             float mn = mx;
 #pragma unroll
@@ -817,18 +821,21 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(const CombineA
         const float mx0 = mx;
 #pragma unroll
         for (int g = 1; g < S; ++g) mx = fmaxf(mx, s_max[lane_row + g]);
-        const float w0 = expf(mx0 - mx);
+        const float off = mx == -INFINITY ? 0.f : mx;
+        const float w0 = expf(mx0 - off);
         tot *= w0;
         acc *= w0;
 #pragma unroll
         for (int g = 1; g < S; ++g) {
-            const float w = expf(s_max[lane_row + g] - mx);
+            const float w = expf(s_max[lane_row + g] - off);
             tot += w * s_tot[lane_row + g];
             acc += w * s_acc[threadIdx.x + g * CPR];
         }
     }
-    const float lse_tot = mx + logf(tot);
-    acc *= 1.f / tot;
+    // as in an unsplit item: a row whose weights are all 0 gives 0, one whose sum is NaN
+    // gives NaN (already in acc), both with the log-sum-exp -inf
+    const float lse_tot = tot > 0.f ? mx + logf(tot) : -INFINITY;
+    acc *= tot > 0.f ? 1.f / tot : 0.f;
     const int64_t qrow = (int64_t)(cu + ci.q0 + t) * a.num_q_heads + kvh * a.group + hl;
     u32x2 w2;
     w2[0] = pack_bf16x2(acc[0], acc[1]);

@@ -356,7 +356,8 @@ __global__ __launch_bounds__(64, 2) void attention_small_kernel(const AttnArgs a
 
     const float l_tot = row_sum4(l_run);
     const float inv = l_tot > 0.f ? a.v_scale / l_tot : 0.f;  // v_scale is 1 for bf16 pools
-    const float lse_v = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : -INFINITY;
+    // (a split item passes a NaN sum on to the merge)
+    const float lse_v = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : (it.part >= 0 && l_tot != l_tot ? l_tot : -INFINITY);
     // o[db][v] is element d = 16 db + 4 g4 + v of row j
     if (it.part < 0) {
         if (row_ok) {
