@@ -305,9 +305,6 @@ gc::PlanArgs plan_args(const gc_geometry* geo, const gc_batch* b, const Shape& s
     a.prefix_lens = b->prefix_lens_dev;
     a.cu_new_lens = b->cu_new_lens_dev;
     a.scratch = at<int32_t>(ws, pl.layout.scratch_off);
-    a.unsorted = reinterpret_cast<gc::WorkItem*>(
-        at<char>(ws, pl.layout.scratch_off) +
-        gc::align_up(sizeof(int32_t) * 3 * (size_t)(b->batch + 1), 256));
     a.items = at<gc::WorkItem>(ws, pl.layout.items_off);
     a.combines = at<gc::CombineItem>(ws, pl.layout.combine_off);
     a.status = at<int32_t>(ws, pl.layout.status_off);

@@ -122,9 +122,8 @@ inline WorkspaceLayout workspace_layout(int batch, int64_t items, int64_t combin
     off = align_up(off + sizeof(WorkItem) * (size_t)(items > 0 ? items : 1), 256);
     w.combine_off = off;
     off = align_up(off + sizeof(CombineItem) * (size_t)(combines > 0 ? combines : 1), 256);
-    w.scratch_off = off;  // 3 int32 per request + 1, then the unsorted work list
+    w.scratch_off = off;  // 3 int32 per request + 1
     off = align_up(off + sizeof(int32_t) * 3 * (size_t)(batch + 1), 256);
-    off = align_up(off + sizeof(WorkItem) * (size_t)(items > 0 ? items : 1), 256);
     w.part_lse_off = off;
     off = align_up(off + sizeof(float) * (size_t)partials * num_kv_heads * block_m, 256);
     w.part_o_off = off;
@@ -151,7 +150,6 @@ struct PlanArgs {
     const int32_t* prefix_lens;
     const int32_t* cu_new_lens;
     int32_t* scratch;         // 3 * (batch + 1) int32
-    WorkItem* unsorted;       // [items]
     WorkItem* items;          // [items], in launch order (see group_cost)
     CombineItem* combines;    // [combines]
     int32_t* status;          // status[0] = 0 when the device lengths matched the host's

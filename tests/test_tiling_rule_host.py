@@ -36,3 +36,13 @@ def test_automatic_tiling(P, n, D, want):
     sizes = {t: workspace(lib, g, b.desc, t) for t in (gc.TILES_PREFILL, gc.TILES_WIDE)}
     assert sizes[gc.TILES_PREFILL] != sizes[gc.TILES_WIDE]
     assert workspace(lib, g, b.desc, gc.TILES_AUTO) == sizes[want]
+
+
+def test_a_large_batch_of_short_tiles_fits_the_fixed_scratch():
+    """2 million new tokens of 128 query heads on one KV head at d = 64: about 1 million wide
+    tiles or 2 million 128-row ones (the automatic choice), without partial rows; the work list
+    alone fits the scratch of the call that takes no workspace."""
+    lib = gc.load_library()
+    b = HostBatch(np.zeros(1660, np.int32), np.full(1660, 1250, np.int32))
+    g = geo(Hq=128, Hkv=1, D=64, maxb=2100)
+    assert 32 * int(b.n.sum()) < workspace(lib, g, b.desc, gc.TILES_AUTO) <= gc.NOALLOC_SCRATCH_BYTES
