@@ -10,9 +10,6 @@
 
 namespace {
 
-using gc::RequestCounts;
-
-
 struct Shape {
     int64_t total_tokens = 0;
     int group = 1;
@@ -107,6 +104,19 @@ gc_status check_options(const gc_plan_options* o) {
 constexpr int kWideSplitTiles = 2;
 int device_cus();
 
+// f(key tiles) for every query tile of the batch (block_n: a power of two).
+template <typename F>
+inline void for_each_tile(const gc_batch* b, int tq, int block_n, F&& f) {
+    const int shift = __builtin_ctz((unsigned)block_n);
+    for (int r = 0; r < b->batch; ++r) {
+        const uint32_t P = (uint32_t)b->prefix_lens_host[r], n = (uint32_t)b->new_lens_host[r];
+        for (uint32_t q0 = 0; q0 < n; q0 += (uint32_t)tq) {
+            const uint32_t end = q0 + (uint32_t)tq < n ? q0 + (uint32_t)tq : n;
+            f((int)((P + end + (uint32_t)block_n - 1) >> shift));
+        }
+    }
+}
+
 gc_status choose_tiling(const gc_geometry* geo, const gc_batch* b, const gc_plan_options* o, Shape* sh) {
     const int want = o == nullptr ? GC_TILES_AUTO : o->tiling;
     bool small = false, wide = false;
@@ -123,20 +133,21 @@ gc_status choose_tiling(const gc_geometry* geo, const gc_batch* b, const gc_plan
         }
         if (!small && geo->head_dim == 128) {
             const int tq = gc::tokens_per_tile(sh->group, gc::kWideM);
-            int64_t units = 0, rows = 0, tiles = 0;
+            int64_t units = 0, rows = 0;
             for (int r = 0; r < b->batch; ++r) {
-                const int P = b->prefix_lens_host[r], n = b->new_lens_host[r];
-                rows += (int64_t)n * sh->group;
-                for (int q0 = 0; q0 < n; q0 += tq) {
-                    units += 1;
-                    tiles += gc::key_tiles(P, q0, n - q0 < tq ? n - q0 : tq, gc::kBlockN);
-                }
+                units += gc::ceil_div64(b->new_lens_host[r], tq);
+                rows += (int64_t)b->new_lens_host[r] * sh->group;
             }
             const int64_t cus = device_cus();
             const int64_t grid = units * geo->num_kv_heads;
-            tiles *= geo->num_kv_heads;
-            wide = rows * 100 >= units * gc::kWideM * 85 &&
-                   (grid >= 2 * cus || (grid <= cus && tiles >= kWideSplitTiles * cus));
+            if (rows * 100 >= units * gc::kWideM * 85) {
+                wide = grid >= 2 * cus;
+                if (grid <= cus) {
+                    int64_t tiles = 0;
+                    for_each_tile(b, tq, gc::kBlockN, [&](int kt) { tiles += kt; });
+                    wide = tiles * geo->num_kv_heads >= kWideSplitTiles * cus;
+                }
+            }
         }
     }
     sh->small = small;
@@ -182,45 +193,51 @@ int device_cus() {
 // cached ones: 85 us with 480 128-row items (103 with the 600 of equal shares, 97 with
 // 1000); one request of 512 on 8000: 137 us with 256 wide items (165 with 288).
 constexpr int kSmallMinChunkKeys = 384;
-int64_t resident_slots(const Shape& sh) { return (sh.small ? 4LL : (sh.wide ? 1LL : 2LL)) * device_cus(); }
+constexpr int64_t kMaxSlots = 2048;  // (of 256 compute units: 1024)
+int64_t resident_slots(const Shape& sh) {
+    const int64_t slots = (sh.small ? 4LL : (sh.wide ? 1LL : 2LL)) * device_cus();
+    return slots < kMaxSlots ? slots : kMaxSlots;
+}
 
 int choose_chunk(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
                  const gc_plan_options* o) {
     if (o != nullptr && o->kv_split_tiles != 0) return o->kv_split_tiles > 0 ? o->kv_split_tiles : 0;
-    int64_t units = 0, tiles = 0, max_tiles = 1;
-    for (int r = 0; r < b->batch; ++r) {
-        const int P = b->prefix_lens_host[r], n = b->new_lens_host[r];
-        for (int q0 = 0; q0 < n; q0 += sh.tq) {
-            const int ntok = n - q0 < sh.tq ? n - q0 : sh.tq;
-            const int kt = gc::key_tiles(P, q0, ntok, sh.block_n);
-            units += 1;
-            tiles += kt;
-            if (kt > max_tiles) max_tiles = kt;
-        }
-    }
-    units *= geo->num_kv_heads;
-    tiles *= geo->num_kv_heads;
-    const int64_t target = resident_slots(sh);
-    if (units >= target || units == 0) return 0;
-    int64_t chunk = (tiles + target - 1) / target;
+    const int64_t target = resident_slots(sh), heads = geo->num_kv_heads;
+    int64_t all_units = 0;
+    for (int r = 0; r < b->batch; ++r) all_units += gc::ceil_div64(b->new_lens_host[r], sh.tq);
+    if (all_units * heads >= target || all_units == 0) return 0;
+    const int units = (int)all_units;  // fewer than slots
+    int32_t kts[kMaxSlots];            // their key tiles
+    int max_tiles = 1, at = 0;
+    int64_t tiles = 0;
+    for_each_tile(b, sh.tq, sh.block_n, [&](int kt) {
+        kts[at++] = kt;
+        tiles += kt;
+        if (kt > max_tiles) max_tiles = kt;
+    });
+    const int64_t least = (tiles * heads + target - 1) / target;  // equal shares
     const int min_keys = sh.small ? kSmallMinChunkKeys : 512;
-    if (chunk < min_keys / sh.block_n) chunk = min_keys / sh.block_n;
-    auto items = [&](int64_t ch) {
-        int64_t k = 0;
-        for (int r = 0; r < b->batch; ++r) {
-            const int P = b->prefix_lens_host[r], n = b->new_lens_host[r];
-            for (int q0 = 0; q0 < n; q0 += sh.tq)
-                k += gc::ceil_div64(gc::key_tiles(P, q0, n - q0 < sh.tq ? n - q0 : sh.tq, sh.block_n), ch);
-        }
-        return k * geo->num_kv_heads;
+    int lo = least < min_keys / sh.block_n ? min_keys / sh.block_n : (int)least;  // (least <= max_tiles)
+    if (lo >= max_tiles) return lo;  // unsplit
+    // The smallest chunk whose items fit the slots, per KV head. A chunk of c makes fewer than
+    // tiles / c + units items, which bounds the search from above.
+    const int64_t slots = target / heads;
+    auto items = [&](int c) {  // (exact: a double holds either operand, and quotients below 2^31 apart)
+        int k = units;
+        for (int i = 0; i < units; ++i) k += (int)((double)(kts[i] - 1) / (double)c);
+        return (int64_t)k;
     };
-    int64_t hi = max_tiles;  // unsplit tiles: units < target items
-    while (chunk < hi) {
-        const int64_t mid = (chunk + hi) / 2;
-        if (items(mid) <= target) hi = mid;
-        else chunk = mid + 1;
+    if (items(lo) <= slots) return lo;
+    int hi = max_tiles;  // unsplit tiles: units < slots
+    if (slots > units && (tiles + slots - units - 1) / (slots - units) < hi)
+        hi = (int)((tiles + slots - units - 1) / (slots - units));
+    lo += 1;
+    while (lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        if (items(mid) <= slots) hi = mid;
+        else lo = mid + 1;
     }
-    return chunk > INT32_MAX ? 0 : (int)chunk;
+    return lo;
 }
 
 // Work-list order. Items run in list order, and a list in strict cost order,
@@ -237,17 +254,12 @@ void choose_order(const gc_geometry* geo, const gc_batch* b, const Shape& sh, Pl
     const int64_t tail = (2 * resident_slots(sh) + geo->num_kv_heads - 1) / geo->num_kv_heads;  // items per KV head
     if (pl->items <= tail) return;
     int64_t hist[gc::kCostBuckets] = {};  // items per cost (clamped like the planner's buckets)
-    for (int r = 0; r < b->batch; ++r) {
-        const int P = b->prefix_lens_host[r], n = b->new_lens_host[r];
-        for (int q0 = 0; q0 < n; q0 += sh.tq) {
-            const int ntok = n - q0 < sh.tq ? n - q0 : sh.tq;
-            const int kt = gc::key_tiles(P, q0, ntok, sh.block_n);
-            const int ns = gc::num_splits(kt, pl->chunk);
-            const int lo = kt / ns, n_hi = kt - lo * ns;
-            hist[lo < gc::kCostBuckets - 1 ? lo : gc::kCostBuckets - 1] += ns - n_hi;
-            if (n_hi > 0) hist[lo + 1 < gc::kCostBuckets - 1 ? lo + 1 : gc::kCostBuckets - 1] += n_hi;
-        }
-    }
+    for_each_tile(b, sh.tq, sh.block_n, [&](int kt) {
+        const int ns = gc::num_splits(kt, pl->chunk);
+        const int lo = ns == 1 ? kt : kt / ns, n_hi = kt - lo * ns;
+        hist[lo < gc::kCostBuckets - 1 ? lo : gc::kCostBuckets - 1] += ns - n_hi;
+        if (n_hi > 0) hist[lo + 1 < gc::kCostBuckets - 1 ? lo + 1 : gc::kCostBuckets - 1] += n_hi;
+    });
     int64_t below = 0;
     int c = 0;
     while (c < gc::kCostBuckets && below < tail) below += hist[c++];
@@ -257,21 +269,21 @@ void choose_order(const gc_geometry* geo, const gc_batch* b, const Shape& sh, Pl
 gc_status make_plan(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
                     const gc_plan_options* o, Plan* pl) {
     pl->chunk = choose_chunk(geo, b, sh, o);
-    pl->items = pl->combines = pl->partials = 0;
-    int longest = 0;  // key tiles of the longest request
-    for (int r = 0; r < b->batch; ++r) {
-        const int P = b->prefix_lens_host[r], n = b->new_lens_host[r];
-        const RequestCounts c = gc::request_counts(P, n, sh.tq, pl->chunk, sh.block_n);
-        pl->items += c.items;
-        pl->combines += c.combines;
-        pl->partials += c.partials;
-        if (n > 0) {  // a request's last query tile sees the most keys
-            const int kt = gc::ceil_div(P + n, sh.block_n);
-            if (kt > longest) longest = kt;
-            const int ns = gc::num_splits(kt, pl->chunk);
-            if (ns > pl->max_splits) pl->max_splits = ns;
+    int longest = 0;  // key tiles of the longest query tile
+    const int chunk = pl->chunk;
+    int64_t units = 0, combines = 0, partials = 0;
+    for_each_tile(b, sh.tq, sh.block_n, [&](int kt) {
+        units += 1;
+        if (kt > longest) longest = kt;
+        if (chunk > 0 && kt > chunk) {
+            combines += 1;
+            partials += (uint32_t)(kt + chunk - 1) / (uint32_t)chunk;
         }
-    }
+    });
+    pl->items = units - combines + partials;
+    pl->combines = combines;
+    pl->partials = partials;
+    pl->max_splits = gc::num_splits(longest, chunk);
     if (pl->items > (int64_t)INT32_MAX / geo->num_kv_heads) return GC_ERR_BAD_SHAPE;
     pl->layout = gc::workspace_layout(b->batch, pl->items, pl->combines, pl->partials,
                                       geo->num_kv_heads, geo->head_dim, sh.block_m);

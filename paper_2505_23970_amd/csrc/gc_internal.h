@@ -77,26 +77,6 @@ inline int64_t append_pages_host(const int32_t* prefix, const int32_t* n, int ba
     return u;
 }
 
-struct RequestCounts {
-    int items;     // work items of this request (per KV head)
-    int combines;  // query tiles that were split
-    int partials;  // partial slots (per KV head)
-};
-
-__host__ __device__ inline RequestCounts request_counts(int prefix, int n, int tq, int chunk, int block_n) {
-    RequestCounts c{0, 0, 0};
-    for (int q0 = 0; q0 < n; q0 += tq) {
-        int ntok = n - q0 < tq ? n - q0 : tq;
-        int ns = num_splits(key_tiles(prefix, q0, ntok, block_n), chunk);
-        c.items += ns;
-        if (ns > 1) {
-            c.combines += 1;
-            c.partials += ns;
-        }
-    }
-    return c;
-}
-
 // ---------------------------------------------------------------- workspace
 constexpr size_t kStatusOffset = 0;  // byte offset of the planner's status word in the workspace
 // Work queues of the resident attention launch: kQueues ticket counters and one exit

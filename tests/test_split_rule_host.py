@@ -54,3 +54,31 @@ def test_automatic_chunk_is_the_smallest_that_fits_the_slots(name, tiling, Hq, H
     b = HostBatch(np.array(P), np.array(n))
     g = geo(Hq=Hq, Hkv=Hkv, maxb=2100)
     assert workspace(lib, g, b.desc, 0, tiling) == workspace(lib, g, b.desc, chunk, tiling)
+
+
+def test_the_search_costs_little_beside_the_plan():
+    """Every call plans on the host first, so the search for the chunk must stay near the cost of the
+    passes that any plan makes: at most 2.75 times a plan that never splits (500 decode requests on
+    one KV head: 3.5 times when every probe walked the batch up to the longest tile, now 2.1)."""
+    import time
+    lib = gc.load_library()
+    rng = np.random.default_rng(1)
+    b = HostBatch(rng.lognormal(7, .8, 500).astype(np.int32), np.ones(500, np.int32))
+    g = geo(Hq=8, Hkv=1, maxb=2100)
+
+    def best(split):
+        opt, size, t = gc.PlanOptions(split, 0), ctypes.c_size_t(), []
+        args = (ctypes.byref(g), ctypes.byref(b.desc), ctypes.byref(opt), ctypes.byref(size))
+        for _ in range(60):
+            t0 = time.perf_counter()
+            for _ in range(20):
+                lib.gc_prefix_prefill_workspace_size(*args)
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    ratios = []
+    for _ in range(4):   # (another program on the CPU slows one side of a try)
+        ratios.append(best(0) / best(-1))
+        if ratios[-1] <= 2.75:
+            return
+    raise AssertionError(f"automatic plan over unsplit plan: {ratios}")
