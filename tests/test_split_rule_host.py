@@ -1,7 +1,9 @@
 """The automatic key split on the CPU (256 compute units assumed without a GPU): the
 workspace of the automatic plan is that of the smallest chunk, from the floor up, that
-makes no more work items than resident slots, for every tiling and ragged batches."""
+makes no more work items than resident slots, or of equal shares where those end sooner,
+for every tiling and ragged batches."""
 import ctypes
+import heapq
 
 import numpy as np
 import pytest
@@ -20,11 +22,26 @@ BATCHES = {
     "documents": ([2679, 2063, 3533, 4936, 7059, 4226, 3034, 2702] * 2, [19, 11, 15, 16, 14, 26, 64, 4] * 2),
     "empty_among": ([5000, 900, 0, 7000], [2, 0, 0, 30]),
     "many": (list(range(100, 100 + 37 * 300, 37)), [1] * 300),
+    # near as many query tiles as slots, one long among short ones and ragged: cutting few is no help
+    "near_slots_decode": ([(997 * k) % 4000 + 200 for k in range(121)] + [28000, 9000, 12000], [1] * 124),
+    "near_slots_prefill": ([(2999 * k) % 9000 + 500 for k in range(20)] + [19000], [100 + 37 * k for k in range(21)]),
 }
 
 
 def tiles_of(P, n, tq, bn):
     return [-(-(p + min(q0 + tq, m)) // bn) for p, m in zip(P, n) for q0 in range(0, m, tq)]
+
+
+def busiest_slot(kts, chunk, Hkv, slots):
+    """Greedy: items heaviest first, each to the slot that is free first."""
+    sizes = []
+    for k in kts:
+        ns = max(1, -(-k // chunk))
+        sizes += [k // ns + (i < k % ns) for i in range(ns)] * Hkv
+    load = [0] * slots
+    for s in sorted(sizes, reverse=True):
+        heapq.heapreplace(load, load[0] + s)
+    return max(load)
 
 
 def workspace(lib, g, desc, split, tiling):
@@ -38,7 +55,7 @@ def workspace(lib, g, desc, split, tiling):
 @pytest.mark.parametrize("name", sorted(BATCHES))
 @pytest.mark.parametrize("tiling", sorted(RULES))
 @pytest.mark.parametrize("Hq,Hkv", [(64, 8), (8, 1), (12, 4)])
-def test_automatic_chunk_is_the_smallest_that_fits_the_slots(name, tiling, Hq, Hkv):
+def test_automatic_chunk(name, tiling, Hq, Hkv):
     lib = gc.load_library()
     P, n = BATCHES[name]
     m, bn, per_cu, floor_keys = RULES[tiling]
@@ -47,10 +64,13 @@ def test_automatic_chunk_is_the_smallest_that_fits_the_slots(name, tiling, Hq, H
     if len(kts) * Hkv >= slots:
         chunk = -1                                   # enough whole query tiles
     else:
-        chunk = max(floor_keys // bn, -(-sum(kts) * Hkv // slots))
+        shares = chunk = max(floor_keys // bn, -(-sum(kts) * Hkv // slots))
         while chunk < max(kts) and sum(-(-k // chunk) for k in kts) * Hkv > slots:
             chunk += 1
         assert sum(-(-k // chunk) for k in kts) * Hkv <= slots
+        made = sum(-(-k // shares) for k in kts)
+        if made * 4 <= slots // Hkv * 7 and chunk > max(shares, busiest_slot(kts, shares, Hkv, slots)) * 20 // 17:
+            chunk = shares
     b = HostBatch(np.array(P), np.array(n))
     g = geo(Hq=Hq, Hkv=Hkv, maxb=2100)
     assert workspace(lib, g, b.desc, 0, tiling) == workspace(lib, g, b.desc, chunk, tiling)
@@ -58,27 +78,28 @@ def test_automatic_chunk_is_the_smallest_that_fits_the_slots(name, tiling, Hq, H
 
 def test_the_search_costs_little_beside_the_plan():
     """Every call plans on the host first, so the search for the chunk must stay near the cost of the
-    passes that any plan makes: at most 2.75 times a plan that never splits (500 decode requests on
-    one KV head: 3.5 times when every probe walked the batch up to the longest tile, now 2.1)."""
+    passes that any plan makes: at most 2.9 times a plan that never splits (500 decode requests on
+    one KV head: 4 times when every probe walked the batch up to the longest tile, now 2.3)."""
     import time
     lib = gc.load_library()
     rng = np.random.default_rng(1)
     b = HostBatch(rng.lognormal(7, .8, 500).astype(np.int32), np.ones(500, np.int32))
     g = geo(Hq=8, Hkv=1, maxb=2100)
 
-    def best(split):
-        opt, size, t = gc.PlanOptions(split, 0), ctypes.c_size_t(), []
-        args = (ctypes.byref(g), ctypes.byref(b.desc), ctypes.byref(opt), ctypes.byref(size))
-        for _ in range(60):
-            t0 = time.perf_counter()
-            for _ in range(20):
-                lib.gc_prefix_prefill_workspace_size(*args)
-            t.append(time.perf_counter() - t0)
-        return min(t)
-
-    ratios = []
-    for _ in range(4):   # (another program on the CPU slows one side of a try)
-        ratios.append(best(0) / best(-1))
-        if ratios[-1] <= 2.75:
+    size, calls = ctypes.c_size_t(), []
+    for split in (0, -1):
+        opt = gc.PlanOptions(split, 0)
+        calls.append((ctypes.byref(g), ctypes.byref(b.desc), ctypes.byref(opt), ctypes.byref(size)))
+    ratio = float("inf")
+    for _ in range(8):   # (tries: another program may slow the CPU; both sides in turn)
+        best = [float("inf")] * 2
+        for _ in range(150):
+            for k, args in enumerate(calls):
+                t0 = time.perf_counter()
+                for _ in range(4):
+                    lib.gc_prefix_prefill_workspace_size(*args)
+                best[k] = min(best[k], time.perf_counter() - t0)
+        ratio = min(ratio, best[0] / best[1])
+        if ratio <= 2.9:
             return
-    raise AssertionError(f"automatic plan over unsplit plan: {ratios}")
+    raise AssertionError(f"automatic plan over unsplit plan: {ratio:.2f}")
