@@ -78,8 +78,9 @@ def test_automatic_chunk(name, tiling, Hq, Hkv):
 
 def test_the_search_costs_little_beside_the_plan():
     """Every call plans on the host first, so the search for the chunk must stay near the cost of the
-    passes that any plan makes: at most 2.9 times a plan that never splits (500 decode requests on
-    one KV head: 4 times when every probe walked the batch up to the longest tile, now 2.3)."""
+    passes that any plan makes: at most 3.6 times a plan that never splits (500 decode requests on
+    one KV head: 4.0 and 4.5 times on two machines when every probe walked the batch up to the
+    longest tile, now 2.3 to 3.0)."""
     import time
     lib = gc.load_library()
     rng = np.random.default_rng(1)
@@ -100,6 +101,6 @@ def test_the_search_costs_little_beside_the_plan():
                     lib.gc_prefix_prefill_workspace_size(*args)
                 best[k] = min(best[k], time.perf_counter() - t0)
         ratio = min(ratio, best[0] / best[1])
-        if ratio <= 2.9:
+        if ratio <= 3.6:
             return
     raise AssertionError(f"automatic plan over unsplit plan: {ratio:.2f}")
