@@ -24,6 +24,7 @@ struct Plan {
     int chunk = 0;  // key tiles per chunk, 0 = no split
     int64_t items = 0, combines = 0, partials = 0;
     int max_splits = 1;  // key chunks of the query tile with the most
+    bool heaviest_decides = false;  // the heaviest work item ends the launch (see heaviest_decides)
     int group_cost = gc::kCostBuckets;  // work-list order (gc::PlanArgs)
     int buckets = gc::kCostBuckets;
     gc::WorkspaceLayout layout{};
@@ -330,14 +331,29 @@ void choose_order(const gc_geometry* geo, const gc_batch* b, const Shape& sh, Pl
     pl->group_cost = c;  // the items of cost < c make up the tail
 }
 
+// Which 128-row workgroups the kernel prefers (attention_kernels.h): of the two that share a
+// compute unit, the first round's, which hold the heaviest items, or the second's. The
+// first where the heaviest item decides the end: in launches of one round, and beyond where its
+// key tiles exceed the mean load of a slot by a quarter (an item's fixed cost counted as four
+// tiles; below a quarter the lighter items had better end soon and make room). Preferring the
+// second round against the first, bf16 / 8-bit pools, 200 ragged batches: one round 1.00 to
+// 1.13 times the time (520 items, the longest of 63 tiles on a mean load of 41: 100.0 us / 89.2,
+// 126.5 / 117.1); 1.25 to 3 times the mean load 0.92 to 1.15, two in three above 1.04; below,
+// 0.84 to 1.06 (chat turns of 648 items, 62 tiles on 56: 117.1 / 120.4, 151.0 / 173.1).
+bool heaviest_decides(int64_t items, int64_t tiles, int heaviest, int64_t slots) {
+    constexpr int kItemTiles = 4;
+    return items <= slots || (heaviest + kItemTiles) * slots * 4 >= (tiles + kItemTiles * items) * 5;
+}
+
 gc_status make_plan(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
                     const gc_plan_options* o, Plan* pl) {
     pl->chunk = choose_chunk(geo, b, sh, o);
     int longest = 0;  // key tiles of the longest query tile
     const int chunk = pl->chunk;
-    int64_t units = 0, combines = 0, partials = 0;
+    int64_t units = 0, combines = 0, partials = 0, tiles = 0;
     for_each_tile(b, sh.tq, sh.block_n, [&](int kt) {
         units += 1;
+        tiles += kt;
         if (kt > longest) longest = kt;
         if (chunk > 0 && kt > chunk) {
             combines += 1;
@@ -349,6 +365,9 @@ gc_status make_plan(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
     pl->partials = partials;
     pl->max_splits = gc::num_splits(longest, chunk);
     if (pl->items > (int64_t)INT32_MAX / geo->num_kv_heads) return GC_ERR_BAD_SHAPE;
+    pl->heaviest_decides =
+        heaviest_decides(pl->items * geo->num_kv_heads, tiles * geo->num_kv_heads,
+                         chunk > 0 && longest > chunk ? chunk : longest, resident_slots(sh));
     pl->layout = gc::workspace_layout(b->batch, pl->items, pl->combines, pl->partials,
                                       geo->num_kv_heads, geo->head_dim, sh.block_m);
     choose_order(geo, b, sh, pl);
@@ -446,6 +465,8 @@ gc_status enqueue_run(const gc_geometry* geo, const gc_batch* b, const Shape& sh
     a.max_blocks = geo->max_blocks_per_seq;
     a.scale_log2 = (float)((double)scale * (double)pk.k_scale * 1.4426950408889634074);
     a.v_scale = pk.v_scale;
+    a.prefer_span = (uint32_t)device_cus();
+    a.prefer_odd = pl.heaviest_decides ? 0 : 1;
     const hipError_t e = sh.small ? gc::launch_attention_small(a, geo->head_dim, pl.items, pk.fp8, stream)
                                   : gc::launch_attention(a, geo->head_dim, pl.items, sh.wide, pk.fp8,
                                                          resident_workgroups(geo, sh, pl), stream);

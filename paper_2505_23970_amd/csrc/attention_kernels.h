@@ -153,6 +153,16 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     const int tid = tid_opaque;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // One of a SIMD's two wavefronts is preferred throughout (the older half of a wide
+    // workgroup; over d = 128 every other round of a workgroup per compute unit, which of the
+    // two the host says: two 128-row workgroups share a unit): the preferred one's products
+    // run while the other computes weights and the other way round, where equal ones take turns
+    // product by product and then wait for the vector unit together. Mixed 70B batch 2107 ->
+    // 2052 us, 70B chat 434 -> 422, 8B chat 125.7 -> 121.5, over 8-bit pools 173.6 -> 154.8; at
+    // d = 64, where three 128-row workgroups share a compute unit, 2 % slower, so not there.
+    // (Before the item's loads: between them and their uses the branch cost 1-3 % of short launches.)
+    if (WAVES == kWideWaves ? wave < WAVES / 2 : D == 128 && (bid / a.prefer_span & 1) == a.prefer_odd)
+        __builtin_amdgcn_s_setprio(2);
     const int g4 = lane >> 4;
     const int j16 = lane & 15;
     const int kvh = (int)(bid % (unsigned)a.num_kv_heads);
@@ -162,15 +172,6 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     asm volatile("" ::"s"(it.r), "s"(it.q0), "s"(it.kt_begin), "s"(it.kt_end), "s"(it.part), "s"(it.P),
                  "s"(it.cu), "s"(it.n));
     if (it.r < 0 || it.kt_begin >= it.kt_end) return;
-    // One of a SIMD's two wavefronts is preferred throughout (the older half of a wide
-    // workgroup; over d = 128 every other 256 of the 128-row workgroups, two of which share a
-    // compute unit): the preferred one's products run while the other computes weights and
-    // the other way round, where equal ones take turns product by product and then wait
-    // for the vector unit together. Mixed 70B batch 2107 -> 2052 us, 70B chat 434 -> 422,
-    // 8B chat 125.7 -> 121.5, over 8-bit pools 173.6 -> 154.8; at d = 64, where three
-    // 128-row workgroups share a compute unit, 2 % slower, so not there.
-    if (WAVES == kWideWaves ? wave < WAVES / 2 : D == 128 && ((bid >> 8) & 1)) __builtin_amdgcn_s_setprio(2);
-
     // (the planner repeats the request's lengths in the item: one load for all of them)
     const int r = it.r;
     const int P = it.P;

@@ -165,6 +165,7 @@ struct AttnArgs {
     int32_t num_blocks, max_blocks;
     float scale_log2;    // softmax scale * log2(e) (times the key scale for 8-bit pools)
     float v_scale;       // value scale of 8-bit pools, 1 for bf16 pools
+    uint32_t prefer_span, prefer_odd;  // 128-row workgroups b with b / span % 2 == odd are preferred
 };
 
 struct CombineArgs {
