@@ -185,7 +185,7 @@ int device_cus() {
 // so that the launch fills those slots: the smallest chunk that makes no more items
 // than slots (each query tile's chunks are rounded up, so equal shares of the key
 // tiles make a few items more, which run a round of their own), unless the busiest slot
-// ends 15 % sooner with equal shares; and at least 512 keys
+// ends 8 % sooner with equal shares; and at least 512 keys
 // (384 for small tiles), below which the partial rows and a work item's fixed cost
 // outweigh the shorter chunks.
 // Measured on MI355X (attention and merge, 70B heads): one request of 4100 tokens
@@ -194,43 +194,55 @@ int device_cus() {
 // items (155 with 1150, 162 with 4000). 16 requests of 4 to 64 new tokens on 4000
 // cached ones: 85 us with 480 128-row items (103 with the 600 of equal shares, 97 with
 // 1000); one request of 512 on 8000: 137 us with 256 wide items (165 with 288).
-// Fitting against equal shares, by the shares' busiest slot over the fitting chunk: small tiles
-// 104 us / 109 at 1.28, 141 / 146 at 1.05, 171 / 173 at 0.90, 205 / 202 at 0.75 (124 / 116 over
-// 8-bit pools), 265 / 244 at 0.55, 325 / 260 at 0.34 (992 query tiles on 1024 slots); prefill
-// tiles 82 / 89 at 1.21, 270 / 284 at 1.00, 29 / 38 at 0.94, 234 / 207 at 0.78 (268 / 227).
+// Fitting against equal shares on batches of 0.4 to 1 query tile per slot (1000 of them), by the
+// busiest slot of the shares over the fitting chunk, each with an item's fixed cost in key tiles.
+// Below 0.92 (12/11) prefill tiles lose by fitting (wide: 114 us / 202 at 0.48, 145 / 220 at
+// 0.60, 126 / 159 at 0.69, 66 / 74 at 0.77; 128-row: 230 / 287 at 0.78, 89 / 110 at 0.82), above it
+// they gain (wide 45 / 38 at 1.09, 62 / 47 at 1.21; 128-row 89 / 70 at 0.97, 110 / 89 at 1.25),
+// with an exception in 100 batches. Small tiles are bound by the memory, not by the slot that ends last, so
+// a second item has to save much: 264 / 333 at 0.68, but 59 / 48 at 1.47 and 335 / 278 at 0.95
+// (8-bit pools would gain up to 30 % between 0.8 and 1.1, and share their plans with bf16 ones).
 constexpr int kSmallMinChunkKeys = 384;
+constexpr int kItemTilesSmall = 64, kItemTiles = 16, kItemTilesWide = 5;
 constexpr int64_t kMaxSlots = 2048;  // (of 256 compute units: 1024)
 int64_t resident_slots(const Shape& sh) {
     const int64_t slots = (sh.small ? 4LL : (sh.wide ? 1LL : 2LL)) * device_cus();
     return slots < kMaxSlots ? slots : kMaxSlots;
 }
 
-// Key tiles of the slot that ends last when the query tiles kts[0 .. units) are cut into chunks of
-// c key tiles (every one `heads` times), more items than slots and at most twice as many, and run
-// heaviest first: the items past the slots follow the lightest of the first round, the
-// heaviest of the one after the lightest of the other. (Sizes in at most 512 steps.)
-int busiest_slot(const int32_t* kts, int units, int c, int heads, int64_t slots) {
+// Key tiles, and `fixed` for each item, of the slot that ends last when the query tiles kts[0 .. units)
+// are cut into chunks of c key tiles (every one `heads` times), more items than slots and at most
+// twice as many, and run heaviest first: the items past the slots follow the lightest of the first
+// round, the heaviest of the one after the lightest of the other. (Sizes in at most 512 steps.)
+// partials: the chunks of the query tiles that are cut.
+int busiest_slot(const int32_t* kts, int units, int c, int heads, int64_t slots, int fixed, int64_t* partials) {
     constexpr int kSizes = 512;
     int shift = 0;
     while ((c >> shift) >= kSizes) ++shift;
     const int top = c >> shift;
     int32_t count[kSizes];
     for (int s = 0; s <= top; ++s) count[s] = 0;
-    int64_t items = 0;
+    int whole = 0, cut = 0;  // items of query tiles in one piece, and in several
     for (int i = 0; i < units; ++i) {
-        const int ns = gc::num_splits(kts[i], c);
-        const int lo = ns == 1 ? kts[i] : kts[i] / ns, n_hi = kts[i] - lo * ns;
+        if (kts[i] <= c) {
+            count[kts[i] >> shift] += 1;
+            whole += 1;
+            continue;
+        }
+        const int ns = 1 + (int)((double)(kts[i] - 1) / (double)c);  // (exact, as in choose_chunk)
+        const int lo = (int)((double)kts[i] / (double)ns), n_hi = kts[i] - lo * ns;
         count[lo >> shift] += ns - n_hi;
         if (n_hi > 0) count[(lo + 1) >> shift] += n_hi;
-        items += ns;
+        cut += ns;
     }
-    int64_t past = items * heads - slots;
+    *partials = cut;
+    int64_t past = (int64_t)(whole + cut) * heads - slots;
     // the size `a` at place slots - 1 of the list, then upwards; `b` from place slots downwards
     int a = top;
     int64_t in_a = (int64_t)count[a] * heads, first = slots;
-    int most = 0;
+    int alone = 0, two = 0;  // most tiles of a slot with one item, with two
     while (first > in_a && a > 0) {
-        if (in_a > 0 && most == 0) most = a;
+        if (in_a > 0 && alone == 0) alone = a;
         first -= in_a;
         in_a = (int64_t)count[--a] * heads;
     }
@@ -242,12 +254,14 @@ int busiest_slot(const int32_t* kts, int units, int c, int heads, int64_t slots)
         while (in_b == 0 && b > 0) in_b = (int64_t)count[--b] * heads;
         const int64_t m = in_a < in_b ? in_a : in_b;
         if (m <= 0) break;
-        if (a + b > most) most = a + b;
+        if (a + b > two) two = a + b;
         in_a -= m;
         in_b -= m;
         past -= m;
     }
-    return most << shift;
+    alone = (alone << shift) + fixed;
+    two = (two << shift) + 2 * fixed;
+    return alone > two ? alone : two;
 }
 
 int choose_chunk(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
@@ -285,13 +299,17 @@ int choose_chunk(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
         hi = (int)((tiles + slots - units - 1) / (slots - units));
     // Near as many query tiles as slots, few of them can be cut: where the chunk that fits is far
     // above the load of the busiest slot with equal shares, those are better.
-    // (That slot carries at least the mean load, lo.)
-    auto limit = [](int64_t load) { return load * 20 / 17; };
-    if (limit(lo) < hi && items((int)limit(lo)) <= slots) {
-        hi = (int)limit(lo);
-    } else if (limit(lo) < hi && shares * 4 <= slots * 7) {  // (partial rows within 60 MB)
-        const int64_t fits = limit(busiest_slot(kts, units, lo, (int)heads, target));
-        if (fits < hi) {
+    // (That slot carries at least the mean load.)
+    const int fixed = sh.small ? kItemTilesSmall : sh.wide ? kItemTilesWide : kItemTiles;
+    auto limit = [&](int64_t load) { return load * 12 / 11 - fixed; };
+    const int64_t mean = (tiles + shares * fixed) * heads / target;
+    if (limit(mean) < hi && items((int)limit(mean)) <= slots) {
+        hi = (int)limit(mean);
+    } else if (limit(mean) < hi && shares <= 2 * slots) {
+        int64_t partials;
+        const int64_t fits = limit(busiest_slot(kts, units, lo, (int)heads, target, fixed, &partials));
+        // (partial rows within 60 MB, that the calls on the fixed scratch take the batch)
+        if (fits < hi && partials * heads * sh.block_m * (geo->head_dim + 1) * 4 <= 60000000) {
             if (fits <= lo || items((int)fits) > slots) return lo;
             hi = (int)fits;
         }

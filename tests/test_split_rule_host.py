@@ -11,8 +11,9 @@ import pytest
 import paper_2505_23970_amd as gc
 from test_abi_host import HostBatch, geo
 
-# tiling: (query rows, keys per tile, slots per compute unit, least keys per chunk)
-RULES = {gc.TILES_SMALL: (16, 32, 4, 384), gc.TILES_PREFILL: (128, 64, 2, 512), gc.TILES_WIDE: (256, 64, 1, 512)}
+# tiling: (query rows, keys per tile, slots per compute unit, least keys per chunk, an item's cost in tiles)
+RULES = {gc.TILES_SMALL: (16, 32, 4, 384, 64), gc.TILES_PREFILL: (128, 64, 2, 512, 16),
+         gc.TILES_WIDE: (256, 64, 1, 512, 5)}
 CUS = 256
 
 BATCHES = {
@@ -24,6 +25,9 @@ BATCHES = {
     "many": (list(range(100, 100 + 37 * 300, 37)), [1] * 300),
     # near as many query tiles as slots, one long among short ones and ragged: cutting few is no help
     "near_slots_decode": ([(997 * k) % 4000 + 200 for k in range(121)] + [28000, 9000, 12000], [1] * 124),
+    # the same, but an equal share is so short that a second item's fixed cost is more than it saves
+    "near_slots_short": ([300 + 90 * (k % 5) for k in range(110)] + [2400, 1700, 1200], [1] * 113),
+    "near_slots_chat": ([899, 610, 203, 656, 523, 506], [83, 235, 175, 268, 273, 681]),
     "near_slots_prefill": ([(2999 * k) % 9000 + 500 for k in range(20)] + [19000], [100 + 37 * k for k in range(21)]),
 }
 
@@ -32,7 +36,7 @@ def tiles_of(P, n, tq, bn):
     return [-(-(p + min(q0 + tq, m)) // bn) for p, m in zip(P, n) for q0 in range(0, m, tq)]
 
 
-def busiest_slot(kts, chunk, Hkv, slots):
+def busiest_slot(kts, chunk, Hkv, slots, cost):
     """Greedy: items heaviest first, each to the slot that is free first."""
     sizes = []
     for k in kts:
@@ -40,7 +44,7 @@ def busiest_slot(kts, chunk, Hkv, slots):
         sizes += [k // ns + (i < k % ns) for i in range(ns)] * Hkv
     load = [0] * slots
     for s in sorted(sizes, reverse=True):
-        heapq.heapreplace(load, load[0] + s)
+        heapq.heapreplace(load, load[0] + s + cost)
     return max(load)
 
 
@@ -58,7 +62,7 @@ def workspace(lib, g, desc, split, tiling):
 def test_automatic_chunk(name, tiling, Hq, Hkv):
     lib = gc.load_library()
     P, n = BATCHES[name]
-    m, bn, per_cu, floor_keys = RULES[tiling]
+    m, bn, per_cu, floor_keys, cost = RULES[tiling]
     kts = tiles_of(P, n, m // (Hq // Hkv), bn)
     slots = per_cu * CUS
     if len(kts) * Hkv >= slots:
@@ -69,7 +73,9 @@ def test_automatic_chunk(name, tiling, Hq, Hkv):
             chunk += 1
         assert sum(-(-k // chunk) for k in kts) * Hkv <= slots
         made = sum(-(-k // shares) for k in kts)
-        if made * 4 <= slots // Hkv * 7 and chunk > max(shares, busiest_slot(kts, shares, Hkv, slots)) * 20 // 17:
+        busiest = max(shares + cost, busiest_slot(kts, shares, Hkv, slots, cost))
+        rows = m * Hkv * sum(-(-k // shares) for k in kts if k > shares)
+        if made <= 2 * (slots // Hkv) and rows * (128 + 1) * 4 <= 60e6 and chunk > busiest * 12 // 11 - cost:
             chunk = shares
     b = HostBatch(np.array(P), np.array(n))
     g = geo(Hq=Hq, Hkv=Hkv, maxb=2100)
