@@ -25,6 +25,7 @@ struct Plan {
     int64_t items = 0, combines = 0, partials = 0;
     int max_splits = 1;  // key chunks of the query tile with the most
     bool heaviest_decides = false;  // the heaviest work item ends the launch (see heaviest_decides)
+    bool three = false;             // a third 128-row workgroup per compute unit pays (8-bit pools, d = 64)
     int group_cost = gc::kCostBuckets;  // work-list order (gc::PlanArgs)
     int buckets = gc::kCostBuckets;
     gc::WorkspaceLayout layout{};
@@ -363,6 +364,12 @@ bool heaviest_decides(int64_t items, int64_t tiles, int heaviest, int64_t slots)
     return items <= slots || (heaviest + kItemTiles) * slots * 4 >= (tiles + kItemTiles * items) * 5;
 }
 
+// 8-bit pools at d = 64: 128-row tiles run three workgroups per compute unit, at the price of spilled
+// registers, where there is a third one and the mean load of a slot (two per unit) is long enough
+// for the spills at an item's ends (three workgroups / two: 84.2 us / 95.0 at 58 tiles, 41.1 / 46.7
+// at 28, 69.2 / 74.2 at 17, 30.4 / 30.9 at 15; 24.4 / 23.1 at 11, 22.2 / 21.1 at 9).
+constexpr int kThirdTiles = 13;
+
 gc_status make_plan(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
                     const gc_plan_options* o, Plan* pl) {
     pl->chunk = choose_chunk(geo, b, sh, o);
@@ -383,9 +390,10 @@ gc_status make_plan(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
     pl->partials = partials;
     pl->max_splits = gc::num_splits(longest, chunk);
     if (pl->items > (int64_t)INT32_MAX / geo->num_kv_heads) return GC_ERR_BAD_SHAPE;
-    pl->heaviest_decides =
-        heaviest_decides(pl->items * geo->num_kv_heads, tiles * geo->num_kv_heads,
-                         chunk > 0 && longest > chunk ? chunk : longest, resident_slots(sh));
+    const int64_t slots = resident_slots(sh);
+    pl->heaviest_decides = heaviest_decides(pl->items * geo->num_kv_heads, tiles * geo->num_kv_heads,
+                                            chunk > 0 && longest > chunk ? chunk : longest, slots);
+    pl->three = pl->items * geo->num_kv_heads > slots && tiles * geo->num_kv_heads >= kThirdTiles * slots;
     pl->layout = gc::workspace_layout(b->batch, pl->items, pl->combines, pl->partials,
                                       geo->num_kv_heads, geo->head_dim, sh.block_m);
     choose_order(geo, b, sh, pl);
@@ -486,7 +494,7 @@ gc_status enqueue_run(const gc_geometry* geo, const gc_batch* b, const Shape& sh
     a.prefer_span = (uint32_t)device_cus();
     a.prefer_odd = pl.heaviest_decides ? 0 : 1;
     const hipError_t e = sh.small ? gc::launch_attention_small(a, geo->head_dim, pl.items, pk.fp8, stream)
-                                  : gc::launch_attention(a, geo->head_dim, pl.items, sh.wide, pk.fp8,
+                                  : gc::launch_attention(a, geo->head_dim, pl.items, sh.wide, pl.three, pk.fp8,
                                                          resident_workgroups(geo, sh, pl), stream);
     if (e != hipSuccess) return GC_ERR_HIP;
     if (pl.combines > 0) {

@@ -5,9 +5,9 @@
 
 namespace gc {
 
-hipError_t launch_attention(const AttnArgs& a, int head_dim, int64_t num_items, bool wide, bool fp8,
-                            int resident, hipStream_t s) {
-    if (fp8) return launch_attention_fp8(a, head_dim, num_items, wide, resident, s);
+hipError_t launch_attention(const AttnArgs& a, int head_dim, int64_t num_items, bool wide, bool three,
+                            bool fp8, int resident, hipStream_t s) {
+    if (fp8) return launch_attention_fp8(a, head_dim, num_items, wide, three, resident, s);
     const dim3 grid((unsigned)(num_items * a.num_kv_heads));
     if (resident > 0 && wide) {
         const int total = (int)(num_items * a.num_kv_heads);

@@ -123,7 +123,7 @@ __device__ __forceinline__ void widen_e4m3x16(const u32x4 c, u32x4& lo, u32x4& h
 
 // One work item (a workgroup of WAVES wavefronts): the item of launch index bid (blockIdx.x
 // in the regular launch), i.e. work item bid / Hkv for KV head bid % Hkv.
-template <int D, int WAVES, bool FP8>
+template <int D, int WAVES, bool FP8, int WGS = 8 / WAVES>
 __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned bid) {
     constexpr int kBlockRows = WAVES * kRowsPerWave;  // query rows of a work item
     constexpr int KS = D / 32;                      // k-steps of QK^T
@@ -317,8 +317,9 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     const uint32_t v_at = (uint32_t)((g4 & 1) * kPageBytes + j16 * 32 + 16 * ((g4 >> 1) ^ (j16 >> 3)));
 
     // LDS fragment reads kept in flight ahead of their products (three and five within 1 %,
-    // eight 1-10 % slower)
-    constexpr int kAhead = 4;
+    // eight 1-10 % slower; two for three 128-row workgroups per compute unit over 8-bit pools, whose
+    // 168 registers then spill 12 instead of 16: 1 % faster)
+    constexpr int kAhead = FP8 && WGS * WAVES == 12 ? 2 : 4;
     // hook(i) runs after the products of the i-th K fragment are issued (the next tile's copies go there)
     auto compute_tile = [&](const unsigned char* kb, const unsigned char* vb, int kt, auto&& hook) {
         // S^T = K_tile . Q^T: fragment i is (half i / 2 KS, k-step, block i % 2), used for
@@ -696,9 +697,12 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, const unsigned
     }
 }
 
-template <int D, int WAVES, bool FP8>
-__global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void attention_kernel(const AttnArgs a) {
-    attention_body<D, WAVES, FP8>(a, blockIdx.x);
+// WGS: workgroups per compute unit to compile for. Two wavefronts per SIMD, or three: the 128-row tiles
+// at d = 64 take 164 registers over bf16 pools, and 189 over 8-bit ones, whose third workgroup costs 12
+// spilled registers (the launcher's rule says when it pays).
+template <int D, int WAVES, bool FP8, int WGS = 8 / WAVES>
+__global__ __launch_bounds__(WAVES * 64, WGS) void attention_kernel(const AttnArgs a) {
+    attention_body<D, WAVES, FP8, WGS>(a, blockIdx.x);
 }
 
 // Resident launch (wide tiles): one workgroup per compute unit, each

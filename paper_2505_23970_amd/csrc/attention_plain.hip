@@ -4,8 +4,8 @@
 
 namespace gc {
 
-hipError_t launch_attention_fp8(const AttnArgs& a, int head_dim, int64_t num_items, bool wide, int resident,
-                                hipStream_t s) {
+hipError_t launch_attention_fp8(const AttnArgs& a, int head_dim, int64_t num_items, bool wide, bool three,
+                                int resident, hipStream_t s) {
     const dim3 grid((unsigned)(num_items * a.num_kv_heads));
     if (resident > 0 && wide) {
         const int total = (int)(num_items * a.num_kv_heads);
@@ -24,6 +24,8 @@ hipError_t launch_attention_fp8(const AttnArgs& a, int head_dim, int64_t num_ite
     } else {
         if (head_dim == 128)
             attention_kernel<128, kWaves, true><<<grid, kWaves * 64, 0, s>>>(a);
+        else if (three)
+            attention_kernel<64, kWaves, true, 3><<<grid, kWaves * 64, 0, s>>>(a);
         else
             attention_kernel<64, kWaves, true><<<grid, kWaves * 64, 0, s>>>(a);
     }

@@ -186,11 +186,12 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t s);
 hipError_t launch_prepare(const AppendArgs& aa, const PlanArgs& pa, int head_dim, bool fp8, hipStream_t s);
 // resident > 0 (wide tiles only): that many resident workgroups take
 // the items from the work queues instead of one workgroup per item
-hipError_t launch_attention(const AttnArgs& a, int head_dim, int64_t num_items, bool wide, bool fp8,
+// (three: the 128-row kernel of three workgroups per compute unit over 8-bit pools at d = 64)
+hipError_t launch_attention(const AttnArgs& a, int head_dim, int64_t num_items, bool wide, bool three, bool fp8,
                             int resident, hipStream_t s);
 // the same over 8-bit pools (launch_attention forwards fp8 launches here)
-hipError_t launch_attention_fp8(const AttnArgs& a, int head_dim, int64_t num_items, bool wide, int resident,
-                                hipStream_t s);
+hipError_t launch_attention_fp8(const AttnArgs& a, int head_dim, int64_t num_items, bool wide, bool three,
+                                int resident, hipStream_t s);
 hipError_t launch_attention_small(const AttnArgs& a, int head_dim, int64_t num_items, bool fp8,
                                   hipStream_t s);
 hipError_t launch_read_probe(const void* buf, size_t bytes, uint32_t* sink, hipStream_t s);
