@@ -1,7 +1,8 @@
 """Resident attention launch (GPU): wide tiles (bf16 or 8-bit pools) with at least two
 rounds of work items per compute unit run as one workgroup per CU taking items from per-XCD
 ticket queues in the workspace. The queues must start empty after every plan and be
-left empty by every run, whatever the workspace held before."""
+left empty by every run, whatever the workspace held before. Wide tiles are asked for, since the
+automatic choice takes them at d = 128 only."""
 import sys
 
 import numpy as np
@@ -29,6 +30,19 @@ def gpu_ready():
     gc.load_library()
 
 
+def run_is_resident(run, w, ws, *scales):
+    """Queues that say that every item is taken: a resident launch then writes nothing and sets them
+    back, any other launch does not look at them."""
+    import torch
+    import paper_2505_23970_amd as gc
+    ws[QUEUE_BYTES[0]:QUEUE_BYTES[1] - 4].view(torch.int32).fill_(1 << 20)
+    out = torch.zeros(tuple(w.q.shape), dtype=torch.bfloat16, device="cuda")
+    (gc.run_fp8 if scales else gc.run)(run.q, run.k_pool, run.v_pool, run.batch, w.scale, *scales, ws, out=out,
+                                       tiling=gc.TILES_WIDE)
+    torch.cuda.synchronize()
+    return not out.any().item() and not ws[QUEUE_BYTES[0]:QUEUE_BYTES[1]].any().item()
+
+
 def resident_batch(seed, D=128):
     # 64 q / 8 kv heads: wide tiles of 32 tokens; 4 misses of 1024 tokens and two hits
     # give 139 work items per KV head, 1112 workgroups: more than two per CU
@@ -50,18 +64,19 @@ def test_resident_runs_repeat_bitwise_and_match_the_oracle(D):
     run = H.DeviceRun(w)
     run.append()
     T, Hq, _ = w.q.shape
-    ws = gc.alloc_workspace(Hq, run.k_pool, run.v_pool, run.batch)
+    ws = gc.alloc_workspace(Hq, run.k_pool, run.v_pool, run.batch, tiling=gc.TILES_WIDE)
     ws[QUEUE_BYTES[0]:QUEUE_BYTES[1]] = 0x7F  # left-over counters: the plan must clear them
-    gc.plan(Hq, run.k_pool, run.v_pool, run.batch, ws)
+    gc.plan(Hq, run.k_pool, run.v_pool, run.batch, ws, tiling=gc.TILES_WIDE)
     outs, lses = [], []
     for _ in range(3):
         out = torch.full((T, Hq, D), float("nan"), dtype=torch.bfloat16, device="cuda")
         lse = torch.full((T, Hq), float("nan"), dtype=torch.float32, device="cuda")
-        gc.run(run.q, run.k_pool, run.v_pool, run.batch, w.scale, ws, out=out, lse=lse)
+        gc.run(run.q, run.k_pool, run.v_pool, run.batch, w.scale, ws, out=out, lse=lse, tiling=gc.TILES_WIDE)
         torch.cuda.synchronize()
         outs.append(H.from_dev_bits(out))
         lses.append(lse.cpu().numpy())
         assert not ws[QUEUE_BYTES[0]:QUEUE_BYTES[1]].any().item(), "the run left its ticket counters set"
+    assert run_is_resident(run, w, ws)
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
     assert np.array_equal(lses[0].view(np.uint32), lses[2].view(np.uint32))
     rows = H.sample_rows(w, seed=31)
@@ -126,16 +141,18 @@ def test_resident_launch_over_8bit_pools(D):
     run.append()
     kref, vref = H.oracle_pools_fp8(run)
     T, Hq, _ = w.q.shape
-    ws = gc.alloc_workspace(Hq, run.k_pool, run.v_pool, run.batch)
-    gc.plan(Hq, run.k_pool, run.v_pool, run.batch, ws)
+    ws = gc.alloc_workspace(Hq, run.k_pool, run.v_pool, run.batch, tiling=gc.TILES_WIDE)
+    gc.plan(Hq, run.k_pool, run.v_pool, run.batch, ws, tiling=gc.TILES_WIDE)
     outs = []
     for _ in range(2):
         out = torch.full((T, Hq, D), float("nan"), dtype=torch.bfloat16, device="cuda")
         lse = torch.full((T, Hq), float("nan"), dtype=torch.float32, device="cuda")
-        gc.run_fp8(run.q, run.k_pool, run.v_pool, run.batch, w.scale, ks, vs, ws, out=out, lse=lse)
+        gc.run_fp8(run.q, run.k_pool, run.v_pool, run.batch, w.scale, ks, vs, ws, out=out, lse=lse,
+                   tiling=gc.TILES_WIDE)
         torch.cuda.synchronize()
         outs.append(H.from_dev_bits(out))
         assert not ws[QUEUE_BYTES[0]:QUEUE_BYTES[1]].any().item()
+    assert run_is_resident(run, w, ws, ks, vs)
     assert np.array_equal(outs[0], outs[1])
     rows = H.sample_rows(w, seed=50 + D)
     ref_out, ref_lse = H.oracle_rows_fp8(run, kref, vref, rows=rows)
