@@ -306,7 +306,7 @@ int choose_chunk(const gc_geometry* geo, const gc_batch* b, const Shape& sh,
     const int64_t mean = (tiles + shares * fixed) * heads / target;
     if (limit(mean) < hi && items((int)limit(mean)) <= slots) {
         hi = (int)limit(mean);
-    } else if (limit(mean) < hi && shares <= 2 * slots) {
+    } else if (limit(mean) < hi && shares < 2 * slots) {
         int64_t partials;
         const int64_t fits = limit(busiest_slot(kts, units, lo, (int)heads, target, fixed, &partials));
         // (partial rows within 60 MB, that the calls on the fixed scratch take the batch)
@@ -478,8 +478,6 @@ gc_status enqueue_run(const gc_geometry* geo, const gc_batch* b, const Shape& sh
     a.lse = lse;
     a.part_o = at<float>(ws, pl.layout.part_o_off);
     a.part_lse = at<float>(ws, pl.layout.part_lse_off);
-    a.prefix_lens = b->prefix_lens_dev;
-    a.cu_new_lens = b->cu_new_lens_dev;
     a.block_tables = b->block_tables_dev;
     a.items = at<gc::WorkItem>(ws, pl.layout.items_off);
     a.queues = at<int32_t>(ws, pl.layout.queue_off);
@@ -503,7 +501,6 @@ gc_status enqueue_run(const gc_geometry* geo, const gc_batch* b, const Shape& sh
         c.lse = lse;
         c.part_o = a.part_o;
         c.part_lse = a.part_lse;
-        c.prefix_lens = b->prefix_lens_dev;
         c.cu_new_lens = b->cu_new_lens_dev;
         c.combines = at<gc::CombineItem>(ws, pl.layout.combine_off);
         c.num_q_heads = geo->num_q_heads;
@@ -658,10 +655,11 @@ void* scratch_address(gc_status* st) {
 }
 
 // Append and run from a plan already in the workspace, as two launches. One launch that
-// read the new keys from k_new / v_new and wrote them into the pool from LDS was slower at
-// every size (16 chat requests of the 70B shape 216 us a pass against 179, the 8B chat batch
-// 177 against 143): it read the new keys' values through registers in every tile that holds
-// some, and could not run as a resident launch.
+// read the new keys from k_new / v_new and wrote them into the pool from LDS read the new keys'
+// values through registers in every tile that holds some, and could not run as a resident
+// launch. One / two launches, us a pass, on the same tiles: 16 chat requests of the 70B shape 214 /
+// 195, 8 of the 8B shape 147 / 128, the mixed 70B batch 2547 / 2196, 6 mixed 8B requests 205 / 174;
+// only the smallest calls lose the second launch (one request of 32 tokens 11.7 / 14.1).
 gc_status run_with_append(const gc_geometry* geo, const gc_batch* batch, const gc_plan_options* opts,
                           const void* q, const void* k_new, const void* v_new, void* k_pool, void* v_pool,
                           float scale, void* out, float* lse, void* workspace, size_t workspace_bytes,

@@ -49,8 +49,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLn2 = 0.69314718055994530942f;
-// Buffer resource word 3 for raw (untyped) loads: 32-bit data format.
-constexpr int kBufferFlags = 0x00020000;
 
 // Position of 16-byte chunk `chunk` inside key row `row` of a tile in LDS. A fragment
 // read takes, per 16 lanes, the rows 16 p + 8 h + 4 b + v (p, h = 0, 1, v = 0 .. 3) of one

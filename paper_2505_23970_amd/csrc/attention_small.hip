@@ -31,8 +31,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef const __attribute__((address_space(4))) int32_t* scalar_i32p;
 
 constexpr float kLn2 = 0.69314718055994530942f;
-// Buffer resource word 3 for raw (untyped) loads: 32-bit data format.
-constexpr int kBufferFlags = 0x00020000;
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     const bf16x2 p = {(__bf16)lo, (__bf16)hi};

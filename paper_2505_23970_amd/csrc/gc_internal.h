@@ -156,8 +156,6 @@ struct AttnArgs {
     float* lse;          // may be null
     float* part_o;       // [partials][Hkv][block_m][D]
     float* part_lse;     // [partials][Hkv][block_m]
-    const int32_t* prefix_lens;
-    const int32_t* cu_new_lens;
     const int32_t* block_tables;
     const WorkItem* items;
     int32_t* queues;     // resident launch: [kQueues] ticket counters, then the exit counter
@@ -173,7 +171,6 @@ struct CombineArgs {
     float* lse;
     const float* part_o;
     const float* part_lse;
-    const int32_t* prefix_lens;
     const int32_t* cu_new_lens;
     const CombineItem* combines;
     int32_t num_q_heads, num_kv_heads, group, tq;

@@ -75,7 +75,7 @@ def test_automatic_chunk(name, tiling, Hq, Hkv):
         made = sum(-(-k // shares) for k in kts)
         busiest = max(shares + cost, busiest_slot(kts, shares, Hkv, slots, cost))
         rows = m * Hkv * sum(-(-k // shares) for k in kts if k > shares)
-        if made <= 2 * (slots // Hkv) and rows * (128 + 1) * 4 <= 60e6 and chunk > busiest * 12 // 11 - cost:
+        if made < 2 * (slots // Hkv) and rows * (128 + 1) * 4 <= 60e6 and chunk > busiest * 12 // 11 - cost:
             chunk = shares
     b = HostBatch(np.array(P), np.array(n))
     g = geo(Hq=Hq, Hkv=Hkv, maxb=2100)
