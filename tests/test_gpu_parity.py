@@ -267,8 +267,8 @@ def test_block_relabelling_is_bitwise_invisible():
 def test_pool_beyond_4_gib(kv, tiling):
     """Block ids whose byte offsets exceed 2^32: the same batch run on its own pool and
     with every block id shifted past 4 GiB inside a larger pool gives bitwise the same
-    output, LSE and appended pages ("fused": the shifted run appends inside the
-    attention launch). The blocks that a 32-bit wraparound of those offsets would
+    output, LSE and appended pages ("fused": the shifted run appends in the combined
+    call). The blocks that a 32-bit wraparound of those offsets would
     land on hold NaN, so a truncated offset shows up."""
     import torch
     import paper_2505_23970_amd as gc
@@ -676,7 +676,7 @@ def test_prepare_equals_append_then_plan(kv, split):
     assert same(lse_a, lse_b)
 
 
-# ----------------------------------------------------------------- append fused into the attention launch
+# ----------------------------------------------------------------- append and attention in one call
 
 def same_bits(x, y):
     """Bitwise equality of two device tensors (unused pool slots hold NaN sentinels)."""
@@ -703,7 +703,8 @@ def fused_run(run: H.DeviceRun, kv_split_tiles=None, tiling=None):
 
 
 def fused_equals_separate(w, kv_split_tiles=None, tiling=None):
-    """The fused launch gives the separate append + run's pools, output and LSE bit for bit."""
+    """The combined call gives the separate append + run's pools, output and LSE bit for bit (its two
+    launches are theirs, so this pins that it makes both, in order, on the same plan)."""
     import torch
     say(f"case {w.name}: fused append, B={w.batch} Hq={w.num_q_heads} Hkv={w.num_kv_heads} "
         f"D={w.head_dim} T={w.total_new} split={kv_split_tiles} tiling={tiling}")
@@ -742,13 +743,12 @@ def test_fused_append_configs(k):
 
 
 def test_fused_append_decode_workload():
-    # small tiles: the append is its own launch ahead of the attention
     fused_equals_separate(W.decode_variant())
 
 
 @pytest.mark.parametrize("split", [None, 3])
 def test_fused_append_against_the_oracle(split):
-    """Pools and every output row of the fused launch against the oracle directly."""
+    """Pools and every output row of the combined call against the oracle directly."""
     w = W.build([130, 0, 64, 1500, 17], [200, 70, 64, 1, 95], 16, 2, 128, seed=125, name="fused_oracle")
     say(f"case {w.name}: fused append vs oracle, split {split}")
     kp_ref, vp_ref = H.oracle_pools(w)
