@@ -171,7 +171,7 @@ def auto_kernel_name(w, cus, fp8):
     tiles when every request has n * g <= 16, else at d = 128 wide tiles when 256-row tiles are
     >= 85 % full and either two or more per compute unit or at most one with two key tiles
     per compute unit, run as a resident launch from two rounds of work items on, else
-    128-row tiles)."""
+    128-row tiles; a key split, made of less than one round of query tiles, stays below two)."""
     g = w.num_q_heads // w.num_kv_heads
     D = w.head_dim
     f = "true" if fp8 else "false"
@@ -186,28 +186,10 @@ def auto_kernel_name(w, cus, fp8):
                                  for P, n in zip(w.prefix_lens, w.new_lens) for q0 in range(0, int(n), tq))
     wide = D == 128 and rows * 100 >= units * 256 * 85 and (
         grid >= 2 * cus or (grid <= cus and tiles >= 2 * cus))
-    if wide and cus % 8 == 0 and wide_items(w, cus) * w.num_kv_heads >= 2 * cus:
+    if wide and cus % 8 == 0 and grid >= 2 * cus:
         # resident launch: one workgroup per CU taking the items from per-XCD queues
         return f"attention_resident_kernel<{D}, {f}>" + split
     return f"attention_kernel<{D}, {8 if wide else 4}, {f}>" + split
-
-
-def wide_items(w, cus):
-    """Work items per KV head of the wide tiling (query tiles of 256 rows, cut into key
-    chunks when they do not fill one workgroup per compute unit: the split rule of
-    choose_chunk in the C ABI, restated)."""
-    g = w.num_q_heads // w.num_kv_heads
-    tq = 256 // g
-    tiles = []
-    for P, n in zip(w.prefix_lens, w.new_lens):
-        for q0 in range(0, int(n), tq):
-            ntok = min(tq, int(n) - q0)
-            tiles.append((int(P) + q0 + ntok + 63) // 64)
-    units = len(tiles) * w.num_kv_heads
-    if units == 0 or units >= cus:
-        return len(tiles)
-    chunk = max((sum(tiles) * w.num_kv_heads + cus - 1) // cus, 512 // 64)
-    return sum(1 if kt <= chunk else (kt + chunk - 1) // chunk for kt in tiles)
 
 
 def measured_read_gbs(mib=4096, reps=5):
