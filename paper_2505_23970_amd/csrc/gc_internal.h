@@ -148,7 +148,12 @@ struct PlanArgs {
     int32_t buckets;
 };
 
+// (Integers first: the order decides how the compiler loads and holds the arguments. With the
+// pointers first the wide kernel takes 485 us instead of 476 on 4 x 128 new tokens over 32768.)
 struct AttnArgs {
+    int32_t num_q_heads, num_kv_heads, group, tq;
+    int32_t num_blocks, max_blocks;
+    uint32_t prefer_span, prefer_odd;  // 128-row workgroups b with b / span % 2 == odd are preferred
     const uint16_t* q;
     const uint16_t* k_pool;
     const uint16_t* v_pool;
@@ -159,11 +164,8 @@ struct AttnArgs {
     const int32_t* block_tables;
     const WorkItem* items;
     int32_t* queues;     // resident launch: [kQueues] ticket counters, then the exit counter
-    int32_t num_q_heads, num_kv_heads, group, tq;
-    int32_t num_blocks, max_blocks;
     float scale_log2;    // softmax scale * log2(e) (times the key scale for 8-bit pools)
     float v_scale;       // value scale of 8-bit pools, 1 for bf16 pools
-    uint32_t prefer_span, prefer_odd;  // 128-row workgroups b with b / span % 2 == odd are preferred
 };
 
 struct CombineArgs {
