@@ -189,7 +189,9 @@ def auto_kernel_name(w, cus, fp8):
     if wide and cus % 8 == 0 and grid >= 2 * cus:
         # resident launch: one workgroup per CU taking the items from per-XCD queues
         return f"attention_resident_kernel<{D}, {f}>" + split
-    return f"attention_kernel<{D}, {8 if wide else 4}, {f}>" + split
+    # (the last argument: workgroups per compute unit it is compiled for; 8-bit launches of 128-row
+    # tiles at d = 64 that are long enough take 3)
+    return f"attention_kernel<{D}, {8 if wide else 4}, {f}, {1 if wide else 2}>" + split
 
 
 def measured_read_gbs(mib=4096, reps=5):
