@@ -8,11 +8,13 @@
 // for every page that receives at least one new token, i.e. pages P_r / 16 ..
 // (P_r + n_r - 1) / 16 of every request. The pages of the whole batch are numbered
 // request by request. What bounds it, short of large batches, is the chain of
-// dependent loads of one workgroup: in batches of up to 64 requests every wavefront
-// finds its request by itself, from one load of the lengths and a scan in registers,
-// and the new rows are loaded beside the block-table entry (71 MB at D = 64: 22.3 -> 17.6 us);
-// larger batches take a workgroup-wide scan (256 requests a pass). The page's new
-// slots [s0, s1) are contiguous:
+// dependent loads of one workgroup: launches of up to two workgroups per compute unit
+// over up to 64 requests find their request wavefront by wavefront, from one load of the lengths
+// and a scan in registers; the others take a workgroup-wide scan (256 requests a pass), after which
+// rows that come over PCIe arrive faster (8.8 MB of one KV head 175 us against 184, 17 MB 338 / 345;
+// a barrier after the wavefront's search does not give that; from HBM the two are equal).
+// The new rows are loaded beside the block-table entry (with it and two heads a workgroup, 71 MB at
+// D = 64: 22.3 -> 17.6 us). The page's new slots [s0, s1) are contiguous:
 //   - keys: each slot's row is D contiguous elements in the page, copied in
 //     16-byte chunks (one chunk per thread);
 //   - values: the page is stored transposed ([D][16] slots), so the tokens'
@@ -98,6 +100,8 @@ __device__ __forceinline__ int append_scan(int v, int* s_waves, int* total) {
     return base + x - v;
 }
 
+constexpr int kSearchWorkgroups = 512;  // (see above)
+
 // KV heads one append workgroup serves (the grid's second dimension covers the rest).
 constexpr int append_heads(int head_dim) { return kAppendThreads / (kPage * head_dim / 8); }
 
@@ -115,7 +119,7 @@ __device__ __forceinline__ void append_body(const AppendArgs& a, AppendLds<D>& s
 
     // 1. which request and which of its pages
     int r, P, cu, n, k;
-    if (a.batch <= 64) {
+    if (a.batch <= 64 && a.total_pages * ceil_div(a.num_kv_heads, AppendLds<D>::kHeads) <= kSearchWorkgroups) {
         const int lane = threadIdx.x & 63;
         int c0 = 0, c1 = 0, pre = 0;
         if (lane < a.batch) {

@@ -56,3 +56,15 @@ def test_pools_bit_for_bit(batch, D, Hkv, fp8):
         kp, vp = run.pools() if fp8 else (H.from_dev_bits(run.k_pool), H.from_dev_bits(run.v_pool))
         assert np.array_equal(kp, kp_ref), f"{entry}: k_pool differs at {np.argwhere(kp != kp_ref)[:5]}"
         assert np.array_equal(vp, vp_ref), f"{entry}: v_pool differs at {np.argwhere(vp != vp_ref)[:5]}"
+
+
+@pytest.mark.parametrize("D,Hkv,pages", [(128, 1, 512), (128, 1, 513), (64, 3, 256), (64, 3, 257)])
+def test_both_sides_of_the_search(D, Hkv, pages):
+    """512 workgroups are the last launch whose wavefronts search by themselves."""
+    w = W.build([7, 0, 5], [16 * (pages - 3) + 9, 0, 20], Hkv, Hkv, D, seed=900 + pages, name=f"search_{pages}_d{D}")
+    assert int(sum(-(-(P + n) // 16) - P // 16 for P, n in zip(w.prefix_lens, w.new_lens) if n)) == pages
+    kp_ref, vp_ref = H.oracle_pools(w)
+    run = H.DeviceRun(w)
+    run.append()
+    assert np.array_equal(H.from_dev_bits(run.k_pool), kp_ref)
+    assert np.array_equal(H.from_dev_bits(run.v_pool), vp_ref)
