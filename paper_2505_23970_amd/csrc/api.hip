@@ -100,9 +100,9 @@ gc_status check_options(const gc_plan_options* o) {
 //     22.0 / 23.9, but 26.4 / 25.4 over 8-bit pools).
 // Above two per CU, 128-row tiles win over bf16 pools up to about 140 key tiles per CU (79 / 93
 // at 19, 182 / 189 at 85) and lose 2 to 16 % over 8-bit pools at every size, so wide.
-// Not at d = 64 (half the products for the same weights: the vector unit bounds it, not
-// the copies); three 128-row workgroups share a compute unit there (164 registers) and
-// overlap better: 16 misses of 100 to 1500 tokens 120 us against 148 on wide tiles.
+// Not at d = 64 (half the products for the same weights): three 128-row workgroups share a
+// compute unit there (164 registers) and overlap better: 16 misses of 100 to 1500 tokens 120 us
+// against 148 on wide tiles.
 constexpr int kWideSplitTiles = 2;
 int device_cus();
 
